@@ -594,6 +594,131 @@ __device__ uint32_t block_exclusive_scan_1024(uint32_t v, uint32_t* total, uint3
   return out;
 }
 
+// Exclusive scan over a 1024-thread workgroup of four 16-bit counts packed
+// in a 64-bit word each (no sum of a count may pass 65535); *total gets the
+// packed totals.
+constexpr int kScanWords = 17;
+
+__device__ __forceinline__ uint64_t block_exclusive_scan4_1024(uint64_t v, uint64_t* total,
+                                                               uint64_t* lds17) {
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint64_t incl = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint64_t up = lane_read64(incl, lane >= (uint32_t)o ? lane - o : lane);
+    if (lane >= (uint32_t)o) incl += up;
+  }
+  if (lane == 63) lds17[wave] = incl;
+  __syncthreads();
+  uint64_t before = 0, all = 0;
+#pragma unroll
+  for (uint32_t w = 0; w < 16; ++w) {
+    const uint64_t t = lds17[w];
+    before += w < wave ? t : 0;
+    all += t;
+  }
+  *total = all;
+  return before + incl - v;
+}
+
+// One workgroup of 1024 threads appends the events of up to R rounds of 1024
+// claims, in order: thread t holds the counts, pending events and ids of
+// claims t, t + 1024, ...  One scan of the packed counts places every
+// round's events; each round is built in LDS (s_ev, two events per claim of
+// a round) and copied to the log as contiguous 8-byte words.  All events are
+// appended, or none when they do not fit the log.
+template <int R>
+__device__ __forceinline__ void append_rounds(const uint32_t (&v)[R], const Pend (&pe)[R],
+                                              const uint64_t (&cid)[R], claim_event* s_ev,
+                                              uint64_t* scan, uint64_t ev_cap, Counters* ctr,
+                                              claim_event* __restrict__ log) {
+  const uint64_t base_pos = ctr->log_count, base_seq = ctr->seq_next;
+  uint64_t packed = 0, total;
+#pragma unroll
+  for (int k = 0; k < R; ++k) packed |= (uint64_t)v[k] << (16 * k);
+  const uint64_t at = block_exclusive_scan4_1024(packed, &total, scan);
+  uint64_t all = 0;
+#pragma unroll
+  for (int k = 0; k < R; ++k) all += (total >> (16 * k)) & 0xFFFFu;
+  if (base_pos + all > ev_cap) {
+    if (threadIdx.x == 0) ctr->log_dropped = 1;
+    return;  // uniform: every thread computed the same total
+  }
+  uint64_t run = 0;
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const uint32_t n = (uint32_t)(total >> (16 * k)) & 0xFFFFu;
+    uint32_t i = (uint32_t)(at >> (16 * k)) & 0xFFFFu;
+    if (k && n) __syncthreads();  // s_ev is reused (n is the same for every thread)
+    for (uint32_t e = 0; e < v[k]; ++e, ++i) {
+      claim_event ev;
+      ev.seq = base_seq + run + i;
+      ev.claim_id = cid[k];
+      ev.aux = e == 0 ? pe[k].aux0 : pe[k].aux1;
+      ev.kind = (pe[k].kinds >> (8 * e)) & 0xFFu;
+      ev.block_index = pe[k].j;
+      ev.phys_block = pe[k].phys;
+      ev.reserved = 0;
+      s_ev[i] = ev;
+    }
+    if (n) __syncthreads();
+    const uint64_t* src = (const uint64_t*)s_ev;
+    uint64_t* dst = (uint64_t*)(log + base_pos + run);
+    for (uint32_t w = threadIdx.x; w < n * (sizeof(claim_event) / 8); w += 1024) dst[w] = src[w];
+    run += n;
+  }
+  if (threadIdx.x == 0) {
+    ctr->log_count = base_pos + all;
+    ctr->seq_next = base_seq + all;
+  }
+}
+
+// Mark and compaction of a small batch in one workgroup of 1024 threads: the
+// marks are a bitmap in LDS (one bit per pool block, `words` 32-bit words),
+// a group of 2^lg lanes walks one claim's row, and each thread lists a
+// contiguous share of the bitmap after one scan.
+__device__ __forceinline__ void select_small(const BatchDev& b, uint32_t lg, uint32_t nb, int mode,
+                                             const uint8_t* __restrict__ valid_off,
+                                             const uint32_t* __restrict__ slot_of, uint32_t* bits,
+                                             uint64_t* scan, uint32_t* __restrict__ uniq,
+                                             Counters* ctr) {
+  const uint32_t words = (nb + 31) / 32, t = threadIdx.x;
+  for (uint32_t i = t; i < words; i += 1024) bits[i] = 0;
+  __syncthreads();
+  const uint32_t gl = t & ((1u << lg) - 1);
+  for (uint64_t c = t >> lg; c < b.C; c += 1024u >> lg) {
+    const Row r = read_row(b, c);
+    for (uint32_t j = gl; j < r.n; j += 1u << lg) {
+      const uint32_t blk = b.bi[(uint64_t)r.bo0 + j];
+      if (blk >= nb) continue;
+      if (mode == kMarkOffloaded && !valid_off[blk]) continue;
+      if (mode == kMarkStaged && slot_of[blk] == kNone) continue;
+      atomicOr(bits + (blk >> 5), 1u << (blk & 31));
+    }
+  }
+  __syncthreads();
+  const uint32_t per = (words + 1023) / 1024;
+  const uint32_t w0 = t * per < words ? t * per : words;
+  const uint32_t w1 = w0 + per < words ? w0 + per : words;
+  uint32_t mine = 0;
+  for (uint32_t i = w0; i < w1; ++i) mine += __builtin_popcount(bits[i]);
+  uint64_t total;
+  uint32_t at = (uint32_t)block_exclusive_scan4_1024(mine, &total, scan);
+  for (uint32_t i = w0; i < w1; ++i)
+    for (uint32_t m = bits[i]; m; m &= m - 1) uniq[at++] = i * 32 + __builtin_ctz(m);
+  if (t == 0) ctr->uniq_count = (uint32_t)total;
+}
+
+__global__ void __launch_bounds__(1024) k_select_small(BatchDev b, uint32_t lg, uint32_t nb,
+                                                       int mode,
+                                                       const uint8_t* __restrict__ valid_off,
+                                                       const uint32_t* __restrict__ slot_of,
+                                                       uint32_t* __restrict__ uniq, Counters* ctr) {
+  extern __shared__ uint32_t bits[];
+  __shared__ uint64_t scan[kScanWords];
+  select_small(b, lg, nb, mode, valid_off, slot_of, bits, scan, uniq, ctr);
+}
+
 // Ordered compaction of the marks into the unique-block list (ascending
 // block id).  One workgroup of 1024 threads, 8 marks per thread per step
 // read as one 8-byte word (the mark array is padded to a multiple of 16
@@ -840,6 +965,51 @@ __global__ void __launch_bounds__(kThreads) k_finalize(const uint32_t* __restric
       slot_of[b] = staged ? slot0 + u : kNone;
     } else {
       bres[b].d_res = sum;
+    }
+  }
+}
+
+// The same sums by one workgroup of 1024 threads, for the small batches
+// whose other stages run in one workgroup too: consecutive lanes take
+// consecutive slots t = g * NW + n (one contiguous run of partials per piece
+// group), and with fewer than 1024 slots the piece groups are split over the
+// remaining threads and added in LDS.  store(u, sum) is called once per
+// unique block; the caller's next barrier orders it.
+template <typename Store>
+__device__ __forceinline__ void finalize_small(uint32_t U, const uint64_t* __restrict__ partial,
+                                               uint32_t pgs, uint32_t groups, uint64_t* lds1024,
+                                               Store store) {
+  constexpr uint32_t kBatch = 16;  // loads in flight per thread (32 measured the same)
+  const uint32_t NW = (U + groups - 1) / groups, slots = groups * NW;
+  uint32_t width = 64;
+  while (width < 1024 && width < slots) width <<= 1;
+  const uint32_t splits = 1024 / width, split = threadIdx.x / width;
+  for (uint32_t t0 = 0; t0 < slots; t0 += width) {
+    const uint32_t t = t0 + (threadIdx.x & (width - 1));
+    uint64_t sum = 0;
+    if (t < slots) {
+      const uint64_t* src = partial + t;
+      for (uint32_t pg0 = split; pg0 < pgs; pg0 += kBatch * splits) {
+        uint64_t v[kBatch];
+#pragma unroll
+        for (uint32_t k = 0; k < kBatch; ++k) {
+          const uint32_t pg = pg0 + k * splits;
+          v[k] = pg < pgs ? src[(uint64_t)pg * slots] : 0ull;
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < kBatch; ++k) sum += v[k];
+      }
+    }
+    if (splits > 1) {  // then one pass of the outer loop covers every slot
+      lds1024[threadIdx.x] = sum;
+      __syncthreads();
+      if (split == 0)
+        for (uint32_t k = 1; k < splits; ++k) sum += lds1024[threadIdx.x + k * width];
+      __syncthreads();
+    }
+    if (split == 0 && t < slots) {
+      const uint32_t u = (t % NW) * groups + t / NW;
+      if (u < U) store(u, sum);
     }
   }
 }
@@ -1138,31 +1308,56 @@ __global__ void __launch_bounds__(kThreads) k_unstage(u32x4* __restrict__ pool, 
   }
 }
 
-__global__ void __launch_bounds__(kThreads) k_restore_claims(BatchDev b, RegDev reg,
-                                                             uint32_t* __restrict__ cnt,
-                                                             Pend* __restrict__ pend) {
-  const uint64_t c = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (c >= b.C) return;
+// Claim c moves to RESTORE_REQUIRED if it is well formed, registered and
+// offloaded; returns the number of its events (0 or 1), pe and cid filled.
+__device__ __forceinline__ uint32_t restore_claim(const BatchDev& b, const RegDev& reg, uint64_t c,
+                                                  Pend& pe, uint64_t& cid) {
   const Row r = read_row(b, c);
-  cnt[c] = 0;
-  if (r.malformed) return;
+  if (r.malformed) return 0;
   const int64_t s = reg_find(reg, r.id);
-  if (s < 0) return;
+  if (s < 0) return 0;
   const uint32_t state = reg.e[s].state;
-  if (!(state & kStOffloaded)) return;
+  if (!(state & kStOffloaded)) return 0;
   // a plain store: every lane that finds this claim (a batch may present
   // it twice) stores the same value, and nothing else changes the state
   // while this kernel runs
   if (!(state & kStRestoreRequired)) reg.e[s].state = state | kStRestoreRequired;
-  Pend pe;
   pe.aux0 = reg.e[s].nblk;
   pe.aux1 = 0;
   pe.kinds = CLAIM_EV_RESTORE_REQUIRED;
   pe.j = kNone;
   pe.phys = kNone;
   pe.pad = 0;
-  pend[c] = pe;
-  cnt[c] = 1;
+  cid = r.id;
+  return 1;
+}
+
+__global__ void __launch_bounds__(kThreads) k_restore_claims(BatchDev b, RegDev reg,
+                                                             uint32_t* __restrict__ cnt,
+                                                             Pend* __restrict__ pend) {
+  const uint64_t c = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (c >= b.C) return;
+  Pend pe;
+  uint64_t cid;
+  const uint32_t n = restore_claim(b, reg, c, pe, cid);
+  if (n) pend[c] = pe;
+  cnt[c] = n;
+}
+
+// The same for batches of up to 1024 claims, and their events, in one
+// workgroup and one launch (tiny pool 2.8 us against 2.1 + 2.8 us and a
+// launch; four claims per thread took 21.9 us for 4096 claims against 4.8 +
+// 10 us, so larger batches keep the two kernels).
+__global__ void __launch_bounds__(1024) k_restore_small(BatchDev b, RegDev reg, uint64_t ev_cap,
+                                                        Counters* ctr,
+                                                        claim_event* __restrict__ log) {
+  __shared__ claim_event s_ev[1024];  // at most one event per claim
+  __shared__ uint64_t scan[kScanWords];
+  uint32_t v[1];
+  Pend pe[1];
+  uint64_t cid[1];
+  v[0] = threadIdx.x < b.C ? restore_claim(b, reg, threadIdx.x, pe[0], cid[0]) : 0u;
+  append_rounds<1>(v, pe, cid, s_ev, scan, ev_cap, ctr, log);
 }
 
 // ------------------------------------------------------------------- check
@@ -1171,16 +1366,14 @@ struct CheckState {
   const BlockRes* bres;
 };
 
-template <int W>
-__global__ void __launch_bounds__(kThreads) k_check(BatchDev b, RegDev reg, CheckState st,
-                                                    uint32_t nb, uint32_t bs, uint64_t seed,
-                                                    claim_outcome* __restrict__ out,
-                                                    uint32_t* __restrict__ cnt,
-                                                    Pend* __restrict__ pend) {
-  __shared__ uint64_t tkey[kMaxBlockSize];
-  load_token_keys(tkey, bs, seed);
-  const uint64_t c = group_claim<W>();
-  if (c >= b.C) return;
+// Claim c's outcome and pending events, by its group of W lanes; the event
+// count returned (and o and pe) hold in the group's first lane.  kAhead: a
+// window's loads go out during the previous window (many windows per claim).
+template <int W, bool kAhead>
+__device__ __forceinline__ uint32_t check_claim(const BatchDev& b, const RegDev& reg,
+                                                const CheckState& st, uint32_t nb, uint32_t bs,
+                                                uint64_t seed, const uint64_t* tkey, uint64_t c,
+                                                claim_outcome& o, Pend& pe) {
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t gl = lane & (W - 1), gbase = lane & ~(uint32_t)(W - 1);
   const Row r = read_row(b, c);
@@ -1276,7 +1469,6 @@ __global__ void __launch_bounds__(kThreads) k_check(BatchDev b, RegDev reg, Chec
   // Wide groups (long claims, many windows) load a window's position loads
   // and first token chunk during the previous window, so that a window
   // waits for one round trip (its block records) instead of two.
-  constexpr bool kAhead = W >= 16;
   auto count_of = [&](uint64_t p) { return r.ntok - p * bs < bs ? r.ntok - p * bs : (uint64_t)bs; };
   uint32_t nx_blk = kNone, nx_acc_blk = kNone;
   uint64_t nx_acc_h = 0, nx_acc_d = 0;
@@ -1440,10 +1632,10 @@ __global__ void __launch_bounds__(kThreads) k_check(BatchDev b, RegDev reg, Chec
   }
   reasons = group_or<W>(reasons);
   intact = group_min64<W>(intact);
-  if (gl != 0) return;
+  if (gl != 0) return 0;
 
   const uint64_t best = best_pos < special ? best_pos : special;
-  claim_outcome o;
+  uint32_t events = 1;
   o.claim_id = r.id;
   o.num_blocks = r.n;
   o.reasons = reasons;
@@ -1452,7 +1644,6 @@ __global__ void __launch_bounds__(kThreads) k_check(BatchDev b, RegDev reg, Chec
   o.observed_digest = 0;
   o.chain_hash = h_last;
   o.chain_hash_at_fail = 0;
-  Pend pe;
   pe.pad = 0;
   pe.aux1 = 0;
   if (best == kNoKey) {
@@ -1461,7 +1652,6 @@ __global__ void __launch_bounds__(kThreads) k_check(BatchDev b, RegDev reg, Chec
     o.phys_block = kNone;
     pe.kinds = CLAIM_EV_RESTORED;
     pe.aux0 = h_last;
-    cnt[c] = 1;
   } else {
     const uint32_t cls = (uint32_t)(best >> 32);
     const uint32_t js = (uint32_t)(best & 0xFFFFFFFFull);
@@ -1477,17 +1667,69 @@ __global__ void __launch_bounds__(kThreads) k_check(BatchDev b, RegDev reg, Chec
       pe.kinds = CLAIM_EV_RESTORATION_FAILED | (CLAIM_EV_ACTIVE_REQUEST_REFUSED << 8);
       pe.aux0 = o.observed_digest;
       pe.aux1 = r.id;
-      cnt[c] = 2;
+      events = 2;
     } else {
       pe.kinds = CLAIM_EV_OUTCOME_UNKNOWN;
       pe.aux0 = reasons;
-      cnt[c] = 1;
     }
   }
   pe.j = o.first_failing_block;
   pe.phys = o.phys_block;
+  return events;
+}
+
+template <int W>
+__global__ void __launch_bounds__(kThreads) k_check(BatchDev b, RegDev reg, CheckState st,
+                                                    uint32_t nb, uint32_t bs, uint64_t seed,
+                                                    claim_outcome* __restrict__ out,
+                                                    uint32_t* __restrict__ cnt,
+                                                    Pend* __restrict__ pend) {
+  __shared__ uint64_t tkey[kMaxBlockSize];
+  load_token_keys(tkey, bs, seed);
+  const uint64_t c = group_claim<W>();
+  if (c >= b.C) return;
+  claim_outcome o;
+  Pend pe;
+  const uint32_t events = check_claim<W, (W >= 16)>(b, reg, st, nb, bs, seed, tkey, c, o, pe);
+  if ((threadIdx.x & (W - 1)) != 0) return;
+  cnt[c] = events;
   out[c] = o;
   pend[c] = pe;
+}
+
+// The tail of a small batch's check in one workgroup: the unique blocks'
+// digests, every claim's outcome (one group of W lanes each, all at once:
+// C x W <= 1024) and the ordered events.
+template <int W>
+__global__ void __launch_bounds__(1024) k_check_small(BatchDev b, RegDev reg, CheckState st,
+                                                      uint32_t nb, uint32_t bs, uint64_t seed,
+                                                      const uint32_t* __restrict__ uniq,
+                                                      const uint64_t* __restrict__ partial,
+                                                      uint32_t pgs, uint32_t groups,
+                                                      BlockRes* bres, claim_outcome* out,
+                                                      uint64_t ev_cap, Counters* ctr,
+                                                      claim_event* __restrict__ log) {
+  __shared__ uint64_t tkey[kMaxBlockSize];
+  __shared__ claim_event s_ev[2 * (1024 / W)];
+  __shared__ uint64_t scan[kScanWords];
+  finalize_small(ctr->uniq_count, partial, pgs, groups, tkey,
+                 [&](uint32_t u, uint64_t sum) { bres[uniq[u]].d_res = sum; });
+  load_token_keys(tkey, bs, seed);  // its barrier also orders the digests before their readers
+  uint64_t c = threadIdx.x / W;
+  if constexpr (W == 64) c = __builtin_amdgcn_readfirstlane((uint32_t)c);
+  claim_outcome o;
+  Pend pe[1];
+  uint64_t cid[1] = {0};
+  uint32_t v[1] = {0};
+  if (c < b.C) {
+    const uint32_t events = check_claim<W, (W == 64)>(b, reg, st, nb, bs, seed, tkey, c, o, pe[0]);
+    if ((threadIdx.x & (W - 1)) == 0) {
+      out[c] = o;
+      cid[0] = o.claim_id;
+      v[0] = events;
+    }
+  }
+  append_rounds<1>(v, pe, cid, s_ev, scan, ev_cap, ctr, log);
 }
 
 // ------------------------------------------------------------------ lookup
@@ -1686,69 +1928,36 @@ __global__ void __launch_bounds__(kThreads) k_lookup(BatchDev b, IdDev ids,
 
 // ------------------------------------------------------------ event append
 
-// Batches of up to kSmallEvents claims: one workgroup of 1024 threads
-// appends the events and advances the log, in one launch.  It takes the
-// claims in rounds of 1024, one per thread: coalesced loads of the counts,
-// pending records and ids, a scan of the counts, the round's events built in
-// LDS and copied to the log as contiguous 8-byte words.  (Four claims per
-// thread with each thread storing its own events took 15.6 us for 4096
-// claims.)
+// Batches of up to 1024 R claims: one workgroup of 1024 threads appends the
+// events and advances the log, in one launch.  The counts, pending records
+// and ids of every round are loaded before the one scan that places them
+// (append_rounds).
 constexpr uint64_t kSmallEvents = 4096;
 
+template <int R>
 __global__ void __launch_bounds__(1024) k_events_small(const uint32_t* __restrict__ cnt,
                                                        const Pend* __restrict__ pend,
                                                        const uint64_t* __restrict__ ids, uint64_t C,
-                                                       uint64_t ev_cap, Counters* __restrict__ ctr,
+                                                       uint64_t ev_cap, Counters* ctr,
                                                        claim_event* __restrict__ log) {
-  __shared__ uint32_t lds[17];
   __shared__ claim_event s_ev[2 * 1024];
-  const uint64_t base_pos = ctr->log_count, base_seq = ctr->seq_next;
-  // the call's events, counted first: all of them are appended, or none
-  uint64_t all = 0;
-  for (uint64_t c0 = 0; c0 < C; c0 += 1024) {
-    const uint64_t c = c0 + threadIdx.x;
-    uint32_t total;
-    (void)block_exclusive_scan_1024(c < C ? cnt[c] : 0u, &total, lds);
-    all += total;
-  }
-  if (base_pos + all > ev_cap) {
-    if (threadIdx.x == 0) ctr->log_dropped = 1;
-    return;  // uniform: every thread computed the same total
-  }
-  uint64_t run = 0;
-  for (uint64_t c0 = 0; c0 < C; c0 += 1024) {
-    const uint64_t c = c0 + threadIdx.x;
-    const uint32_t v = c < C ? cnt[c] : 0u;
-    Pend pe;
-    uint64_t cid = 0;
-    if (v) {
-      pe = pend[c];
-      cid = ids[c];
+  __shared__ uint64_t scan[kScanWords];
+  uint32_t v[R];
+  Pend pe[R];
+  uint64_t cid[R];
+  // the records are loaded beside the counts, not after them (a record
+  // without events holds an earlier call's values, which are not used)
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    const uint64_t c = (uint64_t)k * 1024 + threadIdx.x;
+    v[k] = 0;
+    if (c < C) {
+      v[k] = cnt[c];
+      pe[k] = pend[c];
+      cid[k] = ids[c];
     }
-    uint32_t total;
-    uint32_t at = block_exclusive_scan_1024(v, &total, lds);  // also orders the LDS reuse
-    for (uint32_t e = 0; e < v; ++e, ++at) {
-      claim_event ev;
-      ev.seq = base_seq + run + at;
-      ev.claim_id = cid;
-      ev.aux = e == 0 ? pe.aux0 : pe.aux1;
-      ev.kind = (pe.kinds >> (8 * e)) & 0xFFu;
-      ev.block_index = pe.j;
-      ev.phys_block = pe.phys;
-      ev.reserved = 0;
-      s_ev[at] = ev;
-    }
-    __syncthreads();
-    const uint64_t* src = (const uint64_t*)s_ev;
-    uint64_t* dst = (uint64_t*)(log + base_pos + run);
-    for (uint32_t i = threadIdx.x; i < total * (sizeof(claim_event) / 8); i += 1024) dst[i] = src[i];
-    run += total;
-    __syncthreads();  // s_ev is reused by the next round
   }
-  if (threadIdx.x == 0) {
-    ctr->log_count = base_pos + run;
-    ctr->seq_next = base_seq + run;
-  }
+  append_rounds<R>(v, pe, cid, s_ev, scan, ev_cap, ctr, log);
 }
 
 __global__ void __launch_bounds__(kThreads) k_tile_sums(const uint32_t* __restrict__ cnt,
@@ -2138,8 +2347,44 @@ int ensure_claim_scratch(claim_pool* P, uint64_t C, bool for_check) {
   return CLAIM_OK;
 }
 
+// Batches small enough that one workgroup does a stage faster than the
+// several it is split over otherwise: a launch behind another costs about
+// 2.5 us beside its work, and 3-4 us of host time.
+//
+// Selection: the claims in one round of 1024 lanes, and a pool whose bitmap
+// takes at most 32 KiB of LDS.  Measured against k_mark and k_compact: one
+// check waited for 0.6-2.4 us shorter up to 1024 lanes, checks queued behind
+// each other the same; 2048 lanes 0.5 us shorter and 0.5 us longer, 4096
+// lanes 2 us longer both ways.
+constexpr uint64_t kSelectLanes = 1024;  // C x W
+constexpr uint32_t kSelectBlocks = 32768 * 8;
+// Tail: the claims in one round of 1024 lanes, at most kTailRefs positions
+// (one CU hashes them) and kTailPartials partials (one CU reads them).
+// Measured, one check waited for (separate launches -> k_check_small): 64
+// piece groups, 8 / 128 / 256 / 512 / 1024 blocks 32.6 -> 27.3, 67.8 ->
+// 63.1, 106 -> 102, 183 -> 181, 322 -> 326 us, whatever the split into
+// claims; 2 piece groups, 64 / 512 / 1024 positions 29.9 -> 26.3, 34 -> 31,
+// 40 -> 38.5 us.  So 512 blocks of 64 piece groups still gain and 1024 lose.
+constexpr uint64_t kTailRefs = 1024, kTailPartials = 32768;
+
+bool select_is_small(const claim_pool* P, const claim_batch* b) {
+  return P->nb <= kSelectBlocks && (uint64_t)b->num_claims * group_width(b) <= kSelectLanes;
+}
+
+bool check_is_small(const claim_pool* P, const claim_batch* b) {
+  const uint64_t ub = std::min<uint64_t>(b->num_refs, P->nb);
+  return b->num_claims > 0 && b->num_refs <= kTailRefs &&
+         (uint64_t)b->num_claims * group_width(b) <= 1024 && ub * P->pgs <= kTailPartials;
+}
+
 // Mark + compact the blocks referenced by the batch into P->uniq.
 int select_blocks(claim_pool* P, const claim_batch* b, int mode) {
+  if (select_is_small(P, b)) {
+    const uint32_t lg = (uint32_t)__builtin_ctz((unsigned)group_width(b));
+    hipLaunchKernelGGL(k_select_small, dim3(1), dim3(1024), (P->nb + 31) / 32 * 4, P->stream,
+                       batch_dev(b), lg, P->nb, mode, P->valid_off, P->slot_of, P->uniq, P->ctr);
+    return hip_status(hipGetLastError());
+  }
   if (b->num_claims) {
     const BatchDev bd = batch_dev(b);
     const int W = group_width(b);
@@ -2236,8 +2481,12 @@ int append_events(claim_pool* P, const claim_batch* b, ClaimScratch sc) {
   const uint64_t C = b->num_claims;
   if (C == 0) return CLAIM_OK;
   if (C <= kSmallEvents) {
-    hipLaunchKernelGGL(k_events_small, dim3(1), dim3(1024), 0, P->stream, sc.cnt, sc.pend,
-                       b->claim_ids, C, P->ev_cap, P->ctr, P->log);
+    if (C <= 1024)
+      hipLaunchKernelGGL(k_events_small<1>, dim3(1), dim3(1024), 0, P->stream, sc.cnt, sc.pend,
+                         b->claim_ids, C, P->ev_cap, P->ctr, P->log);
+    else
+      hipLaunchKernelGGL(k_events_small<4>, dim3(1), dim3(1024), 0, P->stream, sc.cnt, sc.pend,
+                         b->claim_ids, C, P->ev_cap, P->ctr, P->log);
     return hip_status(hipGetLastError());
   }
   const uint64_t ntiles = (C + kTile - 1) / kTile;
@@ -2751,7 +3000,11 @@ int claim_restore(claim_pool* P, const claim_batch* b, const void* staging,
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(P->stream));
   }
-  if (C) {
+  if (C && C <= 1024) {
+    hipLaunchKernelGGL(k_restore_small, dim3(1), dim3(1024), 0, P->stream, batch_dev(b), reg_dev(P),
+                       P->ev_cap, P->ctr, P->log);
+    HIP_TRY(hipGetLastError());
+  } else if (C) {
     hipLaunchKernelGGL(k_restore_claims, dim3(grid_for(C, 0x7FFFFFFFu)), dim3(kThreads), 0,
                        P->stream, batch_dev(b), reg_dev(P), P->cnt, P->pend);
     HIP_TRY(hipGetLastError());
@@ -2764,6 +3017,28 @@ int claim_restore(claim_pool* P, const claim_batch* b, const void* staging,
 }  // extern "C"
 
 namespace {
+
+int launch_check_small(claim_pool* P, const claim_batch* b, DigestGrid gr, CheckState st,
+                       claim_outcome* out) {
+  switch (group_width(b)) {
+#define CHECK_CASE(w)                                                                            \
+  case w:                                                                                        \
+    hipLaunchKernelGGL(k_check_small<w>, dim3(1), dim3(1024), 0, P->stream, batch_dev(b),        \
+                       reg_dev(P), st, P->nb, P->bs, P->seed, P->uniq, P->partial, P->pgs,       \
+                       gr.groups, P->bres, out, P->ev_cap, P->ctr, P->log);                      \
+    break;
+    CHECK_CASE(2)
+    CHECK_CASE(4)
+    CHECK_CASE(8)
+    CHECK_CASE(16)
+    CHECK_CASE(32)
+    CHECK_CASE(64)
+#undef CHECK_CASE
+    default:
+      return CLAIM_EINVAL;
+  }
+  return hip_status(hipGetLastError());
+}
 
 // The check itself: outcomes to `out`, per-claim scratch in `sc`.
 int check_body(claim_pool* P, const claim_batch* b, claim_outcome* out, ClaimScratch sc) {
@@ -2779,17 +3054,21 @@ int check_body(claim_pool* P, const claim_batch* b, claim_outcome* out, ClaimScr
   const DigestGrid gr = digest_grid(P, b->num_refs);
   TRY(launch_digest(P, gr, P->partial, nullptr));
   TRY(record_stage(P, slot, 2));
-  TRY(launch_finalize(P, gr, 1, 0));
-  TRY(record_stage(P, slot, 3));
-  if (C) {
-    CheckState st;
-    st.bres = P->bres;
-    LAUNCH_GROUPED(k_check, P, b, batch_dev(b), reg_dev(P), st, P->nb, P->bs, P->seed, out,
-                   sc.cnt, sc.pend);
+  CheckState st;
+  st.bres = P->bres;
+  // with stage timing every stage stays a launch of its own
+  if (!(P->flags & CLAIM_POOL_STAGE_TIMING) && check_is_small(P, b)) {
+    TRY(launch_check_small(P, b, gr, st, out));
+  } else {
+    TRY(launch_finalize(P, gr, 1, 0));
+    TRY(record_stage(P, slot, 3));
+    if (C)
+      LAUNCH_GROUPED(k_check, P, b, batch_dev(b), reg_dev(P), st, P->nb, P->bs, P->seed, out,
+                     sc.cnt, sc.pend);
+    TRY(record_stage(P, slot, 4));
+    TRY(append_events(P, b, sc));
+    TRY(record_stage(P, slot, 5));
   }
-  TRY(record_stage(P, slot, 4));
-  TRY(append_events(P, b, sc));
-  TRY(record_stage(P, slot, 5));
   if (P->flags & CLAIM_POOL_TIMING) {
     P->t_head = (P->t_head + 1) % kTimingSlots;
     P->t_count += 1;
