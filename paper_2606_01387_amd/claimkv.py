@@ -37,6 +37,7 @@ NONE = 0xFFFFFFFF
 RESERVED_ID = 0xFFFFFFFFFFFFFFFF
 POOL_TIMING = 0x1
 POOL_STAGE_TIMING = 0x2
+LOOKUP_PINNED = 4096  # requests whose results lookup() takes in page-locked memory
 
 OUTCOME_DTYPE = np.dtype(
     [("claim_id", "<u8"), ("code", "<u4"), ("first_failing_block", "<u4"), ("phys_block", "<u4"),
@@ -252,6 +253,7 @@ class Pool:
         # needs them alive until that work completes, which the next call
         # that waits for the stream guarantees
         self._inflight = []
+        self._lookup_out = None
 
     def close(self) -> None:
         h = getattr(self, "_h", None)
@@ -259,6 +261,7 @@ class Pool:
             _check(lib().claim_pool_destroy(h), "claim_pool_destroy")
         self._h = None
         self._inflight = []
+        self._lookup_out = None
 
     def __del__(self):
         try:
@@ -337,10 +340,23 @@ class Pool:
 
     def lookup(self, batch: DeviceBatch) -> np.ndarray:
         """Reuse lookup of the batch's token rows, read back to the host."""
-        out = self.lookup_async(batch)
+        n = batch.num_claims
+        if n > LOOKUP_PINNED:
+            out = self.lookup_async(batch)
+            self.stream.synchronize()
+            self._inflight = []
+            return out.cpu().numpy().view(LOOKUP_DTYPE)[:n].copy()
+        # few results: the kernel writes them to page-locked memory (kept by
+        # the pool, at most LOOKUP_PINNED records), which saves the copy back
+        if self._lookup_out is None or self._lookup_out[0].numel() < n * LOOKUP_DTYPE.itemsize:
+            mem = _torch().empty(max(64, n) * LOOKUP_DTYPE.itemsize, dtype=_torch().uint8,
+                                 pin_memory=True)
+            self._lookup_out = (mem, mem.numpy().view(LOOKUP_DTYPE))
+        mem, records = self._lookup_out
+        self.lookup_async(batch, out=mem)
         self.stream.synchronize()
         self._inflight = []
-        return out.cpu().numpy().view(LOOKUP_DTYPE)[: batch.num_claims].copy()
+        return records[:n].copy()
 
     def identity_stats(self) -> tuple[int, int]:
         """(registered identities, ambiguous identities)."""
