@@ -286,6 +286,19 @@ struct Counters {  // device-resident counters of one pool (72 bytes)
 
 static_assert(sizeof(Counters) == 72, "Counters layout");
 
+// Copies the counters to the host's page-locked copy, where the host reads
+// them after one wait for the stream (a blit copy would be one more launch).
+// Every thread of the workgroup calls it.  The fence makes this workgroup's
+// own stores visible; the loads bypass the caches, since earlier atomics on
+// the line were performed past them.
+__device__ __forceinline__ void publish_counters(const Counters* ctr, Counters* host) {
+  __threadfence();
+  __syncthreads();
+  if (threadIdx.x < sizeof(Counters) / 8)
+    ((uint64_t*)host)[threadIdx.x] = __hip_atomic_load((const uint64_t*)ctr + threadIdx.x,
+                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // call_pos of a call whose events do not fit the log: they are dropped, all
 // of them, and log_dropped is set.  The host bounds every call it queues
 // itself; the device bound keeps the log in bounds for work the host cannot
@@ -631,7 +644,8 @@ template <int R>
 __device__ __forceinline__ void append_rounds(const uint32_t (&v)[R], const Pend (&pe)[R],
                                               const uint64_t (&cid)[R], claim_event* s_ev,
                                               uint64_t* scan, uint64_t ev_cap, Counters* ctr,
-                                              claim_event* __restrict__ log) {
+                                              claim_event* __restrict__ log,
+                                              Counters* host = nullptr) {
   const uint64_t base_pos = ctr->log_count, base_seq = ctr->seq_next;
   uint64_t packed = 0, total;
 #pragma unroll
@@ -640,9 +654,10 @@ __device__ __forceinline__ void append_rounds(const uint32_t (&v)[R], const Pend
   uint64_t all = 0;
 #pragma unroll
   for (int k = 0; k < R; ++k) all += (total >> (16 * k)) & 0xFFFFu;
-  if (base_pos + all > ev_cap) {
+  if (base_pos + all > ev_cap) {  // uniform: every thread computed the same total
     if (threadIdx.x == 0) ctr->log_dropped = 1;
-    return;  // uniform: every thread computed the same total
+    if (host) publish_counters(ctr, host);
+    return;
   }
   uint64_t run = 0;
 #pragma unroll
@@ -671,6 +686,7 @@ __device__ __forceinline__ void append_rounds(const uint32_t (&v)[R], const Pend
     ctr->log_count = base_pos + all;
     ctr->seq_next = base_seq + all;
   }
+  if (host) publish_counters(ctr, host);
 }
 
 // Mark and compaction of a small batch in one workgroup of 1024 threads: the
@@ -723,10 +739,11 @@ __global__ void __launch_bounds__(1024) k_select_small(BatchDev b, uint32_t lg, 
 // block id).  One workgroup of 1024 threads, 8 marks per thread per step
 // read as one 8-byte word (the mark array is padded to a multiple of 16
 // bytes with zeros); a step's indices are gathered in LDS and written out
-// with coalesced stores; clears the marks it reads.
+// with coalesced stores; clears the marks it reads.  With `host` it then
+// publishes the counters (an offload's verdict).
 __global__ void __launch_bounds__(1024) k_compact(uint8_t* __restrict__ mark, uint32_t nb,
-                                                  uint32_t* __restrict__ uniq,
-                                                  Counters* __restrict__ ctr) {
+                                                  uint32_t* __restrict__ uniq, Counters* ctr,
+                                                  Counters* host) {
   constexpr uint32_t kPer = 8;
   __shared__ uint32_t lds[17];
   __shared__ uint32_t out[1024 * kPer];
@@ -754,6 +771,7 @@ __global__ void __launch_bounds__(1024) k_compact(uint8_t* __restrict__ mark, ui
     __syncthreads();
   }
   if (threadIdx.x == 0) ctr->uniq_count = base;
+  if (host) publish_counters(ctr, host);
 }
 
 // ----------------------------------------------------------- digest kernel
@@ -1044,6 +1062,15 @@ __global__ void __launch_bounds__(kThreads) k_dupcheck(BatchDev b, RegDev reg,
   }
 }
 
+// Clears the duplicate check's hash set and flags in one launch.
+__global__ void __launch_bounds__(kThreads) k_dup_clear(unsigned long long* __restrict__ table,
+                                                        uint64_t n, Counters* __restrict__ ctr) {
+  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+  const uint64_t first = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (uint64_t i = first; i < n; i += stride) table[i] = (unsigned long long)kEmptyId;
+  if (first == 0) ctr->dup_flag = 0;
+}
+
 // Store offsets for a batch whose block rows may share entries (some row
 // runs backwards): each well-formed claim gets a run of its own in the
 // footprint and identity stores, at fp_base plus the exclusive prefix sum of
@@ -1079,21 +1106,17 @@ __global__ void __launch_bounds__(1024) k_footprint_offsets(BatchDev b, uint64_t
 // each in-range block: the offload digest ran before acceptance), its
 // accepted identities and their registration, and the record of its
 // ACCEPTED (+ OFFLOADED) events.
+// With owner_at it also raises each block's latest registration
+// (register_owners says how).
+// Returns the claim's event count (held, like pe, in the group's first lane).
 template <int W>
-__global__ void __launch_bounds__(kThreads) k_accept(BatchDev b, RegDev reg, IdDev ids,
-                                                     uint32_t nb, uint32_t bs, uint64_t seed,
-                                                     uint64_t fp_base,
-                                                     const uint64_t* __restrict__ fpo,
-                                                     const uint64_t* __restrict__ d_off,
-                                                     uint32_t* __restrict__ fp_out,
-                                                     Counters* __restrict__ ctr,
-                                                     uint32_t* __restrict__ cnt,
-                                                     Pend* __restrict__ pend, uint64_t c_lo,
-                                                     uint64_t c_hi) {
-  __shared__ uint64_t tkey[kMaxBlockSize];
-  load_token_keys(tkey, bs, seed);
-  const uint64_t c = c_lo + group_claim<W>();  // claims [c_lo, c_hi) of the batch
-  if (c >= c_hi) return;
+__device__ __forceinline__ uint32_t accept_claim(const BatchDev& b, const RegDev& reg,
+                                                 const IdDev& ids, uint32_t nb, uint32_t bs,
+                                                 uint64_t seed, const uint64_t* tkey,
+                                                 uint64_t fp_base, const uint64_t* fpo,
+                                                 const uint64_t* d_off, uint32_t* fp_out,
+                                                 uint64_t* owner_at, Counters* ctr, uint64_t c,
+                                                 Pend& pe) {
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t gl = lane & (W - 1), gbase = lane & ~(uint32_t)(W - 1);
   const Row r = read_row(b, c);
@@ -1126,77 +1149,106 @@ __global__ void __launch_bounds__(kThreads) k_accept(BatchDev b, RegDev reg, IdD
     uint32_t res = 0;
     if (j < npos) {
       reg.idn[at0 + j] = my_h;
-      if (offloaded) res = id_insert(ids, my_h, b.bi[(uint64_t)r.bo0 + j], at0 + j, at0 + npos);
+      if (offloaded) {
+        const uint32_t blk = b.bi[(uint64_t)r.bo0 + j];
+        if (owner_at)  // nothing waits for it before the next kernel or fence
+          atomicMax((unsigned long long*)(owner_at + blk), (unsigned long long)(at0 + j + 1));
+        res = id_insert(ids, my_h, blk, at0 + j, at0 + npos);
+      }
     }
     wave_count(&ctr->id_entries, res & kRegNewEntry);
   }
-  if (gl != 0) return;
-  if (r.malformed) {
-    cnt[c] = 0;
-    return;
-  }
-  // the claim is registered by k_register_claims, one lane per claim, from
-  // this record (its chain hash and whether it was offloaded)
-  Pend pe;
+  if (gl != 0 || r.malformed) return 0;
+  // the claim is registered from this record (its chain hash and whether it
+  // was offloaded)
   pe.aux0 = h;
   pe.aux1 = r.n;
   pe.kinds = CLAIM_EV_ACCEPTED | (offloaded ? (CLAIM_EV_OFFLOADED << 8) : 0u);
   pe.j = kNone;
   pe.phys = kNone;
   pe.pad = 0;
-  pend[c] = pe;
-  cnt[c] = offloaded ? 2 : 1;
+  return offloaded ? 2 : 1;
 }
 
-// Registration of the batch's claims in the registry, one lane per claim,
-// after acceptance: a read of each probed slot first, then one CAS on the
-// key of an empty one (the batch's ids are distinct and none is registered,
-// which the duplicate check established, so a lost CAS only means another
-// claim took the slot).  Kept out of the claim-group kernel so that each
-// wave waits on its atomics once, for 64 claims.
+template <int W>
+__global__ void __launch_bounds__(kThreads) k_accept(BatchDev b, RegDev reg, IdDev ids,
+                                                     uint32_t nb, uint32_t bs, uint64_t seed,
+                                                     uint64_t fp_base,
+                                                     const uint64_t* __restrict__ fpo,
+                                                     const uint64_t* __restrict__ d_off,
+                                                     uint32_t* __restrict__ fp_out,
+                                                     uint64_t* owner_at,
+                                                     Counters* __restrict__ ctr,
+                                                     uint32_t* __restrict__ cnt,
+                                                     Pend* __restrict__ pend, uint64_t c_lo,
+                                                     uint64_t c_hi) {
+  __shared__ uint64_t tkey[kMaxBlockSize];
+  load_token_keys(tkey, bs, seed);
+  const uint64_t c = c_lo + group_claim<W>();  // claims [c_lo, c_hi) of the batch
+  if (c >= c_hi) return;
+  Pend pe;
+  const uint32_t events =
+      accept_claim<W>(b, reg, ids, nb, bs, seed, tkey, fp_base, fpo, d_off, fp_out, owner_at, ctr,
+                      c, pe);
+  if ((threadIdx.x & (W - 1)) != 0) return;
+  cnt[c] = events;
+  if (events) pend[c] = pe;
+}
+
+// Registration of claim c in the registry, by one lane, after acceptance: a
+// read of each probed slot first, then one CAS on the key of an empty one
+// (the batch's ids are distinct and none is registered, which the duplicate
+// check established, so a lost CAS only means another claim took the slot).
+// Returns whether it was inserted (a malformed row is not).
+__device__ __forceinline__ bool register_claim(const BatchDev& b, const RegDev& reg, uint32_t bs,
+                                               uint64_t fp_base, uint64_t gen, const uint64_t* fpo,
+                                               uint64_t c, const Pend& pe) {
+  const Row r = read_row(b, c);
+  if (r.malformed) return false;
+  uint64_t s = slot_of_id(r.id, reg.mask);
+  bool inserted = false;
+  for (uint64_t probe = 0; probe <= reg.mask; ++probe) {
+    uint64_t k = reg.e[s].key;
+    if (k == kEmptyId)
+      k = atomicCAS((unsigned long long*)&reg.e[s].key, (unsigned long long)kEmptyId,
+                    (unsigned long long)r.id);
+    if (k == kEmptyId) {
+      inserted = true;
+      break;
+    }
+    s = (s + 1) & reg.mask;
+  }
+  // not inserted: unreachable, the host keeps the table at most half full
+  if (!inserted) return false;
+  RegEntry& e = reg.e[s];
+  e.state = kStAccepted | ((pe.kinds >> 8) == CLAIM_EV_OFFLOADED ? kStOffloaded : 0u);
+  e.nblk = r.n;
+  e.ntok = r.ntok;
+  e.chain = pe.aux0;
+  e.fpoff = store_at(fpo, fp_base, c, r.bo0);
+  e.gen = gen;
+  // leading_prefix_at_least(k): the blocks holding the first k tokens
+  uint32_t pred = r.n;
+  if (b.pred) {
+    const uint64_t k = b.pred[c];
+    const uint64_t kb = k / bs + (k % bs != 0);
+    if (kb < r.n) pred = (uint32_t)kb;
+  }
+  e.pred = pred;
+  return true;
+}
+
+// The batch's claims, one lane each: kept out of the claim-group kernel so
+// that each wave waits on its atomics once, for 64 claims.
 __global__ void __launch_bounds__(kThreads) k_register_claims(BatchDev b, RegDev reg, uint32_t bs,
                                                               uint64_t fp_base, uint64_t gen,
                                                               const uint64_t* __restrict__ fpo,
                                                               const Pend* __restrict__ pend,
+                                                              const uint32_t* __restrict__ cnt,
                                                               Counters* __restrict__ ctr) {
   const uint64_t c = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
   bool inserted = false;
-  if (c < b.C) {
-    const Row r = read_row(b, c);
-    if (!r.malformed) {
-      const Pend pe = pend[c];
-      uint64_t s = slot_of_id(r.id, reg.mask);
-      for (uint64_t probe = 0; probe <= reg.mask; ++probe) {
-        uint64_t k = reg.e[s].key;
-        if (k == kEmptyId)
-          k = atomicCAS((unsigned long long*)&reg.e[s].key, (unsigned long long)kEmptyId,
-                        (unsigned long long)r.id);
-        if (k == kEmptyId) {
-          inserted = true;
-          break;
-        }
-        s = (s + 1) & reg.mask;
-      }
-      // not inserted: unreachable, the host keeps the table at most half full
-      if (inserted) {
-        RegEntry& e = reg.e[s];
-        e.state = kStAccepted | ((pe.kinds >> 8) == CLAIM_EV_OFFLOADED ? kStOffloaded : 0u);
-        e.nblk = r.n;
-        e.ntok = r.ntok;
-        e.chain = pe.aux0;
-        e.fpoff = store_at(fpo, fp_base, c, r.bo0);
-        e.gen = gen;
-        // leading_prefix_at_least(k): the blocks holding the first k tokens
-        uint32_t pred = r.n;
-        if (b.pred) {
-          const uint64_t k = b.pred[c];
-          const uint64_t kb = k / bs + (k % bs != 0);
-          if (kb < r.n) pred = (uint32_t)kb;
-        }
-        e.pred = pred;
-      }
-    }
-  }
+  if (c < b.C && cnt[c]) inserted = register_claim(b, reg, bs, fp_base, gen, fpo, c, pend[c]);
   wave_count(&ctr->reg_count, inserted);
 }
 
@@ -1213,15 +1265,11 @@ __global__ void __launch_bounds__(kThreads) k_register_claims(BatchDev b, RegDev
 // before the atomic, so most positions find a later one already there and
 // skip it.
 template <int W>
-__global__ void __launch_bounds__(kThreads) k_register_owners(BatchDev b, RegDev reg, IdDev ids,
-                                                              uint32_t nb, uint32_t bs,
-                                                              uint64_t fp_base,
-                                                              const uint64_t* __restrict__ fpo,
-                                                              uint64_t* __restrict__ owner_at,
-                                                              Counters* __restrict__ ctr) {
-  const uint64_t c_fwd = group_claim<W>();
-  if (c_fwd >= b.C) return;
-  const uint64_t c = b.C - 1 - c_fwd;
+__device__ __forceinline__ void register_owners(const BatchDev& b, const RegDev& reg,
+                                                const IdDev& ids, uint32_t nb, uint32_t bs,
+                                                uint64_t fp_base, const uint64_t* fpo,
+                                                uint64_t* owner_at, Counters* ctr, uint64_t c) {
+  // owner_at null: acceptance has raised it
   const uint32_t gl = (threadIdx.x & 63) & (W - 1);
   const Row r = read_row(b, c);
   const uint64_t nt = (r.ntok + bs - 1) / bs;
@@ -1243,29 +1291,159 @@ __global__ void __launch_bounds__(kThreads) k_register_owners(BatchDev b, RegDev
       if (e && e->block != blk &&
           !(atomicOr((uint32_t*)&e->flags, kIdAmbiguous) & kIdAmbiguous))
         amb = 1;
-      if (*(volatile unsigned long long*)(owner_at + blk) < mine)
+      if (owner_at && *(volatile unsigned long long*)(owner_at + blk) < mine)
         atomicMax((unsigned long long*)(owner_at + blk), mine);
     }
     wave_count(&ctr->id_ambiguous, amb);
   }
 }
 
+template <int W>
+__global__ void __launch_bounds__(kThreads) k_register_owners(BatchDev b, RegDev reg, IdDev ids,
+                                                              uint32_t nb, uint32_t bs,
+                                                              uint64_t fp_base,
+                                                              const uint64_t* __restrict__ fpo,
+                                                              uint64_t* __restrict__ owner_at,
+                                                              Counters* __restrict__ ctr) {
+  const uint64_t c_fwd = group_claim<W>();
+  if (c_fwd >= b.C) return;
+  register_owners<W>(b, reg, ids, nb, bs, fp_base, fpo, owner_at, ctr, b.C - 1 - c_fwd);
+}
+
 // Registration pass 3: each block of the offload whose latest registration
 // belongs to this call (owner_at past the call's first store index) now
 // holds that registration's identity.
+__device__ __forceinline__ void set_holders(uint64_t first, uint64_t stride, const uint32_t* uniq,
+                                            uint32_t U, const uint64_t* owner_at,
+                                            const uint64_t* idn, uint64_t fp_base,
+                                            uint64_t* holder) {
+  for (uint64_t u = first; u < U; u += stride) {
+    const uint32_t b = uniq[u];
+    const uint64_t o = owner_at[b];
+    if (o > fp_base) holder[b] = idn[o - 1];
+  }
+}
+
 __global__ void __launch_bounds__(kThreads) k_holders(const uint32_t* __restrict__ uniq,
                                                       const Counters* __restrict__ ctr,
                                                       const uint64_t* __restrict__ owner_at,
                                                       const uint64_t* __restrict__ idn,
                                                       uint64_t fp_base,
                                                       uint64_t* __restrict__ holder) {
-  const uint32_t U = ctr->uniq_count;
-  const uint64_t stride = (uint64_t)gridDim.x * kThreads;
-  for (uint64_t u = (uint64_t)blockIdx.x * kThreads + threadIdx.x; u < U; u += stride) {
-    const uint32_t b = uniq[u];
-    const uint64_t o = owner_at[b];
-    if (o > fp_base) holder[b] = idn[o - 1];
+  set_holders((uint64_t)blockIdx.x * kThreads + threadIdx.x, (uint64_t)gridDim.x * kThreads, uniq,
+              ctr->uniq_count, owner_at, idn, fp_base, holder);
+}
+
+// Registration after an acceptance that raised owner_at, in one launch: each
+// group's first lane registers its claim, its lanes find duplicate ownership
+// and every thread takes a share of the blocks' holders.
+template <int W>
+__global__ void __launch_bounds__(kThreads) k_register(BatchDev b, RegDev reg, IdDev ids,
+                                                       uint32_t nb, uint32_t bs, uint64_t fp_base,
+                                                       uint64_t gen,
+                                                       const uint64_t* __restrict__ fpo,
+                                                       const Pend* __restrict__ pend,
+                                                       const uint32_t* __restrict__ cnt,
+                                                       const uint32_t* __restrict__ uniq,
+                                                       const uint64_t* __restrict__ owner_at,
+                                                       uint64_t* __restrict__ holder,
+                                                       Counters* __restrict__ ctr) {
+  const uint64_t c = group_claim<W>();
+  if (c < b.C) {
+    register_owners<W>(b, reg, ids, nb, bs, fp_base, fpo, nullptr, ctr, c);
+    bool inserted = false;
+    if ((threadIdx.x & (W - 1)) == 0 && cnt[c])
+      inserted = register_claim(b, reg, bs, fp_base, gen, fpo, c, pend[c]);
+    wave_count(&ctr->reg_count, inserted);
   }
+  set_holders((uint64_t)blockIdx.x * kThreads + threadIdx.x, (uint64_t)gridDim.x * kThreads, uniq,
+              ctr->uniq_count, owner_at, reg.idn, fp_base, holder);
+}
+
+// The front of a small offload in one workgroup: the duplicate check (ids of
+// the batch in an LDS hash set, and against the registry), the selection,
+// and the verdict published to the host.  Up to kFrontClaims claims.
+constexpr uint32_t kFrontClaims = 1024;
+
+__global__ void __launch_bounds__(1024) k_admit_select(BatchDev b, RegDev reg, uint32_t lg,
+                                                       uint32_t nb, uint32_t* __restrict__ uniq,
+                                                       Counters* ctr, Counters* host) {
+  extern __shared__ uint32_t bits[];
+  __shared__ unsigned long long table[2 * kFrontClaims];
+  __shared__ uint64_t scan[kScanWords];
+  __shared__ uint32_t flags;
+  const uint32_t t = threadIdx.x;
+  table[t] = table[t + 1024] = (unsigned long long)kEmptyId;
+  if (t == 0) flags = 0;
+  __syncthreads();
+  if (t < b.C) {
+    uint32_t f = b.bo[t + 1] < b.bo[t] ? kFlagBackwardRow : 0u;
+    const uint64_t id = b.ids[t];
+    if (id != kEmptyId) {
+      uint32_t s = (uint32_t)slot_of_id(id, 2 * kFrontClaims - 1);
+      for (;;) {  // at most half full: an empty slot or the id itself is met
+        const unsigned long long old =
+            atomicCAS(table + s, (unsigned long long)kEmptyId, (unsigned long long)id);
+        if (old == kEmptyId) break;
+        if (old == id) {
+          f |= kFlagDupId;
+          break;
+        }
+        s = (s + 1) & (2 * kFrontClaims - 1);
+      }
+      if (reg_find(reg, id) >= 0) f |= kFlagDupId;
+    }
+    if (f) atomicOr(&flags, f);
+  }
+  select_small(b, lg, nb, kMarkAny, nullptr, nullptr, bits, scan, uniq, ctr);
+  if (t == 0) ctr->dup_flag = flags;  // select_small's barriers ordered the flags
+  publish_counters(ctr, host);
+}
+
+// The rest of a small offload in one workgroup, after its digest: the
+// blocks' digests, acceptance (one group of W lanes per claim, all at once:
+// C x W <= 1024), then, past a fence (they read what other waves' atomics
+// and stores left), duplicate ownership and the blocks' holders, the events,
+// and the counters published to the host.
+template <int W>
+__global__ void __launch_bounds__(1024) k_admit_small(
+    BatchDev b, RegDev reg, IdDev ids, uint32_t nb, uint32_t bs, uint64_t seed, uint64_t fp_base,
+    uint64_t gen, const uint32_t* __restrict__ uniq, const uint64_t* __restrict__ partial,
+    uint32_t pgs, uint32_t groups, int staged, uint32_t slot0, uint64_t* d_off, uint8_t* valid_off,
+    uint32_t* slot_of, uint32_t* fp_out, uint64_t* owner_at, uint64_t* holder, uint64_t ev_cap,
+    Counters* ctr, claim_event* __restrict__ log, Counters* host) {
+  __shared__ uint64_t tkey[kMaxBlockSize];
+  __shared__ claim_event s_ev[2 * (1024 / W)];
+  __shared__ uint64_t scan[kScanWords];
+  const uint32_t U = ctr->uniq_count;
+  finalize_small(U, partial, pgs, groups, tkey, [&](uint32_t u, uint64_t sum) {
+    const uint32_t blk = uniq[u];
+    d_off[blk] = sum;
+    valid_off[blk] = 1;
+    slot_of[blk] = staged ? slot0 + u : kNone;
+  });
+  load_token_keys(tkey, bs, seed);  // its barrier also orders the digests before their readers
+  uint64_t c = threadIdx.x / W;
+  if constexpr (W == 64) c = __builtin_amdgcn_readfirstlane((uint32_t)c);
+  Pend pe[1];
+  uint64_t cid[1] = {0};
+  uint32_t v[1] = {0};
+  bool inserted = false;
+  if (c < b.C) {
+    const uint32_t events = accept_claim<W>(b, reg, ids, nb, bs, seed, tkey, fp_base, nullptr,
+                                            d_off, fp_out, owner_at, ctr, c, pe[0]);
+    if ((threadIdx.x & (W - 1)) == 0 && events) {
+      v[0] = events;
+      cid[0] = b.ids[c];
+      inserted = register_claim(b, reg, bs, fp_base, gen, nullptr, c, pe[0]);
+    }
+  }
+  wave_count(&ctr->reg_count, inserted);
+  __threadfence();
+  __syncthreads();
+  if (c < b.C) register_owners<W>(b, reg, ids, nb, bs, fp_base, nullptr, nullptr, ctr, c);
+  set_holders(threadIdx.x, 1024, uniq, U, owner_at, reg.idn, fp_base, holder);
+  append_rounds<1>(v, pe, cid, s_ev, scan, ev_cap, ctr, log, host);
 }
 
 __global__ void __launch_bounds__(kThreads) k_flips(uint32_t* __restrict__ pool32, uint32_t nb,
@@ -1939,7 +2117,8 @@ __global__ void __launch_bounds__(1024) k_events_small(const uint32_t* __restric
                                                        const Pend* __restrict__ pend,
                                                        const uint64_t* __restrict__ ids, uint64_t C,
                                                        uint64_t ev_cap, Counters* ctr,
-                                                       claim_event* __restrict__ log) {
+                                                       claim_event* __restrict__ log,
+                                                       Counters* host) {
   __shared__ claim_event s_ev[2 * 1024];
   __shared__ uint64_t scan[kScanWords];
   uint32_t v[R];
@@ -1957,7 +2136,7 @@ __global__ void __launch_bounds__(1024) k_events_small(const uint32_t* __restric
       cid[k] = ids[c];
     }
   }
-  append_rounds<R>(v, pe, cid, s_ev, scan, ev_cap, ctr, log);
+  append_rounds<R>(v, pe, cid, s_ev, scan, ev_cap, ctr, log, host);
 }
 
 __global__ void __launch_bounds__(kThreads) k_tile_sums(const uint32_t* __restrict__ cnt,
@@ -1978,7 +2157,8 @@ __global__ void __launch_bounds__(kThreads) k_tile_sums(const uint32_t* __restri
 // One workgroup: exclusive scan of the tile sums; reserves the call's range
 // of the log.
 __global__ void __launch_bounds__(1024) k_scan_tiles(uint32_t* __restrict__ tsum, uint64_t ntiles,
-                                                     uint64_t ev_cap, Counters* __restrict__ ctr) {
+                                                     uint64_t ev_cap, Counters* ctr,
+                                                     Counters* host) {
   __shared__ uint32_t lds[17];
   __shared__ uint64_t run;
   if (threadIdx.x == 0) run = 0;
@@ -2005,6 +2185,7 @@ __global__ void __launch_bounds__(1024) k_scan_tiles(uint32_t* __restrict__ tsum
       ctr->seq_next += run;
     }
   }
+  if (host) publish_counters(ctr, host);
 }
 
 // Writes the events of one tile of kTile claims in rounds of 256 claims,
@@ -2217,6 +2398,8 @@ struct claim_pool {
 
   Counters* ctr = nullptr;
   Counters* host_ctr = nullptr;  // pinned
+  Counters* host_ctr_dev = nullptr;  // its device address
+  hipEvent_t verdict = nullptr;      // an offload's verdict is in host_ctr
   // pinned, kReadBytes: outcomes_read's header, then the records of a small
   // read on their way to the caller's memory
   uint8_t* host_read = nullptr;
@@ -2421,6 +2604,15 @@ bool select_is_small(const claim_pool* P, const claim_batch* b) {
   return P->nb <= kSelectBlocks && (uint64_t)b->num_claims * group_width(b) <= kSelectLanes;
 }
 
+// An offload's front (duplicate check and selection): the host waits for its
+// verdict, so its launches count whole.
+constexpr uint64_t kFrontLanes = 8192;  // C x W
+
+bool front_is_small(const claim_pool* P, const claim_batch* b) {
+  return P->nb <= kSelectBlocks && b->num_claims <= kFrontClaims &&
+         (uint64_t)b->num_claims * group_width(b) <= kFrontLanes;
+}
+
 bool check_is_small(const claim_pool* P, const claim_batch* b) {
   const uint64_t ub = std::min<uint64_t>(b->num_refs, P->nb);
   return b->num_claims > 0 && b->num_refs <= kTailRefs &&
@@ -2428,8 +2620,8 @@ bool check_is_small(const claim_pool* P, const claim_batch* b) {
 }
 
 // Mark + compact the blocks referenced by the batch into P->uniq.
-int select_blocks(claim_pool* P, const claim_batch* b, int mode) {
-  if (select_is_small(P, b)) {
+int select_blocks(claim_pool* P, const claim_batch* b, int mode, Counters* host = nullptr) {
+  if (!host && select_is_small(P, b)) {
     const uint32_t lg = (uint32_t)__builtin_ctz((unsigned)group_width(b));
     hipLaunchKernelGGL(k_select_small, dim3(1), dim3(1024), (P->nb + 31) / 32 * 4, P->stream,
                        batch_dev(b), lg, P->nb, mode, P->valid_off, P->slot_of, P->uniq, P->ctr);
@@ -2457,7 +2649,8 @@ int select_blocks(claim_pool* P, const claim_batch* b, int mode) {
     }
     HIP_TRY(hipGetLastError());
   }
-  hipLaunchKernelGGL(k_compact, dim3(1), dim3(1024), 0, P->stream, P->mark, P->nb, P->uniq, P->ctr);
+  hipLaunchKernelGGL(k_compact, dim3(1), dim3(1024), 0, P->stream, P->mark, P->nb, P->uniq, P->ctr,
+                     host);
   return hip_status(hipGetLastError());
 }
 
@@ -2526,17 +2719,18 @@ struct ClaimScratch {
 
 ClaimScratch pool_scratch(claim_pool* P) { return ClaimScratch{P->cnt, P->pend, P->tsum}; }
 
-// Scan the per-claim event counts and append the events.
-int append_events(claim_pool* P, const claim_batch* b, ClaimScratch sc) {
+// Scan the per-claim event counts and append the events; with `host` the
+// counters are published there.
+int append_events(claim_pool* P, const claim_batch* b, ClaimScratch sc, Counters* host = nullptr) {
   const uint64_t C = b->num_claims;
   if (C == 0) return CLAIM_OK;
   if (C <= kSmallEvents) {
     if (C <= 1024)
       hipLaunchKernelGGL(k_events_small<1>, dim3(1), dim3(1024), 0, P->stream, sc.cnt, sc.pend,
-                         b->claim_ids, C, P->ev_cap, P->ctr, P->log);
+                         b->claim_ids, C, P->ev_cap, P->ctr, P->log, host);
     else
       hipLaunchKernelGGL(k_events_small<4>, dim3(1), dim3(1024), 0, P->stream, sc.cnt, sc.pend,
-                         b->claim_ids, C, P->ev_cap, P->ctr, P->log);
+                         b->claim_ids, C, P->ev_cap, P->ctr, P->log, host);
     return hip_status(hipGetLastError());
   }
   const uint64_t ntiles = (C + kTile - 1) / kTile;
@@ -2544,7 +2738,7 @@ int append_events(claim_pool* P, const claim_batch* b, ClaimScratch sc) {
                      sc.tsum);
   HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(1024), 0, P->stream, sc.tsum, ntiles, P->ev_cap,
-                     P->ctr);
+                     P->ctr, host);
   HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL(k_write_events, dim3((uint32_t)ntiles), dim3(kThreads), 0, P->stream, sc.cnt,
                      sc.pend, b->claim_ids, C, sc.tsum, P->ctr, P->log);
@@ -2720,6 +2914,7 @@ void free_pool(claim_pool* P) {
     if (p) dfree(p);
   if (P->host_ctr) (void)hipHostFree(P->host_ctr);
   if (P->host_read) (void)hipHostFree(P->host_read);
+  if (P->verdict) (void)hipEventDestroy(P->verdict);
   if (P->tev_made)
     for (int i = 0; i < kTimingSlots; ++i)
       for (int s = 0; s < kStages; ++s) (void)hipEventDestroy(P->tev[i][s]);
@@ -2775,7 +2970,7 @@ int read_direct(claim_pool* P, claim_outcome* out, uint64_t nout, claim_event* e
     if (!to_out || !to_ev) return CLAIM_OK;
   }
   volatile ReadHeader* hdr = (volatile ReadHeader*)P->host_read;
-  // 32 words per thread up to 256 workgroups, which keep the host link busy
+  // 8 words per thread up to 256 workgroups, which keep the host link busy
   // (10^6 claims, 148 MB: 2605 us, 57 GB/s)
   const uint32_t grid = grid_for((out_bytes + ev_bytes) / 64, 256);
   hipLaunchKernelGGL(k_read, dim3(grid), dim3(kThreads), 0, P->stream, (const uint64_t*)P->outcomes,
@@ -2925,6 +3120,11 @@ int claim_pool_create(const claim_pool_desc* d, claim_pool** out) {
       rc = CLAIM_ENOMEM;
       break;
     }
+    if (hipHostGetDevicePointer((void**)&P->host_ctr_dev, P->host_ctr, 0) != hipSuccess ||
+        hipEventCreateWithFlags(&P->verdict, hipEventDisableTiming) != hipSuccess) {
+      rc = CLAIM_EHIP;
+      break;
+    }
     if (hipHostMalloc((void**)&P->host_read, kReadBytes, hipHostMallocDefault) != hipSuccess) {
       P->host_read = nullptr;
       rc = CLAIM_ENOMEM;
@@ -2976,6 +3176,42 @@ int claim_pool_destroy(claim_pool* P) {
 // together no better.
 constexpr uint64_t kAcceptFirst = 4096;
 
+// Positions up to which acceptance raises owner_at itself, so that one
+// k_register does what k_register_claims, k_register_owners and k_holders do.
+// Past them acceptance's atomics cost more than the two launches: measured,
+// one offload in three launches / in one: 2048 positions 87.5 / 83.1 us, 2368
+// 87.4 / 84.7, 4096 107.3 / 105.6, 8192 155.2 / 153.5, 10240 152.1 / 159.4,
+// 40960 170.5 / 209.8.
+constexpr uint64_t kMergedRefs = 4096;
+
+namespace {
+
+int launch_admit_small(claim_pool* P, const claim_batch* b, DigestGrid gr, int staged,
+                       uint32_t slot0) {
+  switch (group_width(b)) {
+#define ADMIT_CASE(w)                                                                             \
+  case w:                                                                                         \
+    hipLaunchKernelGGL(k_admit_small<w>, dim3(1), dim3(1024), 0, P->stream, batch_dev(b),         \
+                       reg_dev(P), id_dev(P), P->nb, P->bs, P->seed, P->fp_used, P->gen, P->uniq, \
+                       P->partial, P->pgs, gr.groups, staged, slot0, P->d_off, P->valid_off,      \
+                       P->slot_of, P->fp_store, P->owner_at, P->holder, P->ev_cap, P->ctr,        \
+                       P->log, P->host_ctr_dev);                                                  \
+    break;
+    ADMIT_CASE(2)
+    ADMIT_CASE(4)
+    ADMIT_CASE(8)
+    ADMIT_CASE(16)
+    ADMIT_CASE(32)
+    ADMIT_CASE(64)
+#undef ADMIT_CASE
+    default:
+      return CLAIM_EINVAL;
+  }
+  return hip_status(hipGetLastError());
+}
+
+}  // namespace
+
 int claim_offload(claim_pool* P, const claim_batch* b, void* staging, uint64_t staging_bytes) {
   if (!P || ((uintptr_t)staging & 15)) return CLAIM_EINVAL;
   TRY(check_batch(P, b));
@@ -2985,18 +3221,35 @@ int claim_offload(claim_pool* P, const claim_batch* b, void* staging, uint64_t s
   TRY(ensure_claim_scratch(P, C, false));
 
   // verdict: duplicates and the staged size, before any state changes
-  TRY(fill<uint32_t>(P, &P->ctr->dup_flag, 1, 0u));
   const BatchDev bd = batch_dev(b);
   const RegDev rd = reg_dev(P);
-  if (C) {
-    TRY(fill<unsigned long long>(P, P->dup_table, P->dup_cap, (unsigned long long)kEmptyId));
-    hipLaunchKernelGGL(k_dupcheck, dim3(grid_for(C, 0x7FFFFFFFu)), dim3(kThreads), 0, P->stream, bd,
-                       rd, P->dup_table, P->dup_cap - 1, P->ctr);
+  if (front_is_small(P, b)) {
+    hipLaunchKernelGGL(k_admit_select, dim3(1), dim3(1024), (P->nb + 31) / 32 * 4, P->stream, bd, rd,
+                       (uint32_t)__builtin_ctz((unsigned)group_width(b)), P->nb, P->uniq, P->ctr,
+                       P->host_ctr_dev);
     HIP_TRY(hipGetLastError());
+  } else {
+    hipLaunchKernelGGL(k_dup_clear, dim3(grid_for(P->dup_cap, 4096)), dim3(kThreads), 0, P->stream,
+                       P->dup_table, P->dup_cap, P->ctr);
+    HIP_TRY(hipGetLastError());
+    if (C) {
+      hipLaunchKernelGGL(k_dupcheck, dim3(grid_for(C, 0x7FFFFFFFu)), dim3(kThreads), 0, P->stream,
+                         bd, rd, P->dup_table, P->dup_cap - 1, P->ctr);
+      HIP_TRY(hipGetLastError());
+    }
+    TRY(select_blocks(P, b, kMarkAny, P->host_ctr_dev));
   }
-  TRY(select_blocks(P, b, kMarkAny));
-  TRY(read_counters(P));
-  if (P->host_ctr->dup_flag & kFlagDupId) return CLAIM_EDUP;
+  // The host waits for the verdict alone.  Without staging the digest (it
+  // writes only scratch) is queued before the wait, so that the wait and the
+  // launches after it hide behind it.
+  HIP_TRY(hipEventRecord(P->verdict, P->stream));
+  const DigestGrid gr = digest_grid(P, b->num_refs);
+  if (!staging) TRY(launch_digest(P, gr, P->partial, nullptr));
+  HIP_TRY(hipEventSynchronize(P->verdict));  // the kernels published the counters
+  if (P->host_ctr->dup_flag & kFlagDupId) {
+    HIP_TRY(hipStreamSynchronize(P->stream));  // a refused call leaves nothing running
+    return CLAIM_EDUP;
+  }
   const uint64_t U = P->host_ctr->uniq_count;
   // staging into the current generation's buffer appends after its slots;
   // any other buffer starts a new generation
@@ -3017,7 +3270,10 @@ int claim_offload(claim_pool* P, const claim_batch* b, void* staging, uint64_t s
     HIP_TRY(hipStreamSynchronize(P->stream));
     fpo = P->fpo;
   }
-  if (P->fp_used + fp_need > P->max_fp) return CLAIM_ENOSPC;  // nothing changed
+  if (P->fp_used + fp_need > P->max_fp) {  // nothing changed
+    HIP_TRY(hipStreamSynchronize(P->stream));
+    return CLAIM_ENOSPC;
+  }
 
   // the offload digest of every block the batch references (staged from
   // slot slot0 of the current generation's buffer; another buffer starts a
@@ -3025,38 +3281,51 @@ int claim_offload(claim_pool* P, const claim_batch* b, void* staging, uint64_t s
   // own offload record
   P->gen += 1;
   if (staging && !append) TRY(fill<uint32_t>(P, P->slot_of, P->nb, kNone));
-  const DigestGrid gr = digest_grid(P, b->num_refs);
-  uint8_t* stage_at = staging ? (uint8_t*)staging + slot0 * P->block_bytes : nullptr;
-  TRY(launch_digest(P, gr, P->partial, stage_at));
-  TRY(launch_finalize(P, gr, 0, staging != nullptr, (uint32_t)slot0));
-  if (C) {
+  if (staging)
+    TRY(launch_digest(P, gr, P->partial, (uint8_t*)staging + slot0 * P->block_bytes));
+  if (!fpo && check_is_small(P, b)) {
+    TRY(launch_admit_small(P, b, gr, staging != nullptr, (uint32_t)slot0));
+  } else {
+    TRY(launch_finalize(P, gr, 0, staging != nullptr, (uint32_t)slot0));
+  }
+  if (C && (fpo || !check_is_small(P, b))) {
     // A large batch's first claims are accepted in a launch of their own:
     // identities that many claims share (common prefixes) are then in the
     // table before the rest start, instead of every resident wave racing
     // to insert them into the same empty slots.
     const int W = group_width(b);
+    const bool merged = b->num_refs <= kMergedRefs;
+    uint64_t* owner_at = merged ? P->owner_at : nullptr;
     const uint64_t first = C > 2 * kAcceptFirst ? kAcceptFirst : C;
     claim_batch part = *b;
     part.num_claims = (uint32_t)first;
     LAUNCH_GROUPED_W(k_accept, P, &part, W, bd, rd, id_dev(P), P->nb, P->bs, P->seed, P->fp_used,
-                     fpo, P->d_off, P->fp_store, P->ctr, P->cnt, P->pend, 0ull, first);
+                     fpo, P->d_off, P->fp_store, owner_at, P->ctr, P->cnt, P->pend, 0ull, first);
     if (C > first) {
       part.num_claims = (uint32_t)(C - first);
       LAUNCH_GROUPED_W(k_accept, P, &part, W, bd, rd, id_dev(P), P->nb, P->bs, P->seed,
-                       P->fp_used, fpo, P->d_off, P->fp_store, P->ctr, P->cnt, P->pend, first,
-                       C);
+                       P->fp_used, fpo, P->d_off, P->fp_store, owner_at, P->ctr, P->cnt, P->pend,
+                       first, C);
     }
-    hipLaunchKernelGGL(k_register_claims, dim3(grid_for(C, 0x7FFFFFFFu)), dim3(kThreads), 0,
-                       P->stream, bd, rd, P->bs, P->fp_used, P->gen, fpo, P->pend, P->ctr);
-    HIP_TRY(hipGetLastError());
-    LAUNCH_GROUPED(k_register_owners, P, b, bd, rd, id_dev(P), P->nb, P->bs, P->fp_used, fpo,
-                   P->owner_at, P->ctr);
-    hipLaunchKernelGGL(k_holders, dim3(grid_for(U ? U : 1, 4096)), dim3(kThreads), 0, P->stream,
-                       P->uniq, P->ctr, P->owner_at, P->idn_store, P->fp_used, P->holder);
-    HIP_TRY(hipGetLastError());
-    TRY(append_events(P, b, pool_scratch(P)));
+    if (merged) {
+      LAUNCH_GROUPED(k_register, P, b, bd, rd, id_dev(P), P->nb, P->bs, P->fp_used, P->gen, fpo,
+                     P->pend, P->cnt, P->uniq, P->owner_at, P->holder, P->ctr);
+    } else {
+      hipLaunchKernelGGL(k_register_claims, dim3(grid_for(C, 0x7FFFFFFFu)), dim3(kThreads), 0,
+                         P->stream, bd, rd, P->bs, P->fp_used, P->gen, fpo, P->pend, P->cnt, P->ctr);
+      HIP_TRY(hipGetLastError());
+      LAUNCH_GROUPED(k_register_owners, P, b, bd, rd, id_dev(P), P->nb, P->bs, P->fp_used, fpo,
+                     P->owner_at, P->ctr);
+      hipLaunchKernelGGL(k_holders, dim3(grid_for(U ? U : 1, 4096)), dim3(kThreads), 0, P->stream,
+                         P->uniq, P->ctr, P->owner_at, P->idn_store, P->fp_used, P->holder);
+      HIP_TRY(hipGetLastError());
+    }
+    TRY(append_events(P, b, pool_scratch(P), P->host_ctr_dev));
   }
-  TRY(read_counters(P));
+  if (C)
+    HIP_TRY(hipStreamSynchronize(P->stream));  // the last kernel published the counters
+  else
+    TRY(read_counters(P));
   P->fp_used += fp_need;
   if (staging) {
     P->stage_base = staging;

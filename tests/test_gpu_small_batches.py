@@ -4,7 +4,9 @@ positions, 32768 partials); larger ones the kernels split over workgroups.
 At and around those edges both must give the oracle's digests, outcomes and
 events: each group width, a claim of several windows, faults, missing
 entries, malformed and empty rows, an event log that just holds the call's
-events, and pools past the LDS bitmap."""
+events, and pools past the LDS bitmap.  An offload's front (up to 1024 claims and 8192 lanes)
+and tail follow the same pattern: acceptance, duplicate ids, identities shared
+within and across batches, backward rows, staging."""
 
 import numpy as np
 import pytest
@@ -97,4 +99,95 @@ def test_small_batch(torch, ck, pool, claims, blocks):
     assert np.array_equal(st["d_off"][recorded], d0[recorded])
     assert np.array_equal(st["d_res"][recorded], d1[recorded])
     del kv
+    free_gpu(torch)
+
+
+# the front's edges: claims 1024 and past, lanes (claims x width) 8192 and past;
+# the tail's: as above
+FRONT = [(1, 3), (16, 64), (17, 64), (32, 20), (33, 20), (128, 64), (129, 64), (512, 2), (513, 2),
+         (1024, 4), (1024, 9), (1025, 1)]
+
+
+def family_batch(g, claims, blocks, rng, base, first=None):
+    """Claims whose leading blocks are often another's, tokens and blocks or
+    tokens alone (the same identity on another block is ambiguous)."""
+    parts = [] if first is None else list(first)
+    made = []
+    for i in range(claims):
+        n = max(1, blocks - int(rng.integers(0, 2)))
+        blk = rng.integers(0, g.num_blocks, n).astype(np.uint32)
+        tok = rng.integers(0, 32000, n * g.block_size).astype(np.uint32)
+        if parts and rng.random() < 0.6:
+            _, b0, t0 = parts[int(rng.integers(len(parts)))]
+            k = int(rng.integers(0, min(n, len(b0), len(t0) // g.block_size) + 1))
+            tok[: k * g.block_size] = t0[: k * g.block_size]
+            if rng.random() < 0.7:
+                blk[:k] = b0[:k]
+        parts.append((base + i, blk, tok))
+        made.append(parts[-1])
+    return made
+
+
+@pytest.mark.parametrize("claims,blocks", FRONT, ids=[f"{c}x{n}" for c, n in FRONT])
+@pytest.mark.parametrize("staged", [False, True], ids=["plain", "staged"])
+def test_small_offload(torch, ck, claims, blocks, staged):
+    g = Geometry(2, 2, 4, 1, 8, 2, 300)
+    rng = np.random.default_rng(claims * 77 + blocks)
+    w = Workload(name="small-offload", geometry=g, seed=78, num_claims=0, length=TINY.length,
+                 sharing=TINY.sharing, corrupt_rate=0.0, gen_seed=1, content_seed=10)
+    one = family_batch(g, claims, blocks, rng, 10)
+    two = family_batch(g, claims, blocks, rng, 100000, first=one)
+    batches = [from_claims(one), from_claims(two)]
+    if claims > 8:  # rows that share entries: one row runs backwards
+        third = from_claims(family_batch(g, claims, blocks, rng, 200000, first=two))
+        third.block_offsets[4] = third.block_offsets[2]
+        batches.append(third)
+    note(f"small offload {claims} x {blocks} {'staged' if staged else ''}")
+    host = content.pool_host(g, w.content_seed)
+    d0 = digests(host, w)
+    op = O.OraclePool(g.num_blocks, g.block_size, w.seed)
+    kv = gpu_pool_tensor(torch, w)
+    refs = sum(b.num_refs for b in batches) + 4 * blocks
+    staging = torch.zeros(3 * 300 * g.block_bytes, dtype=torch.uint8, device="cuda") if staged else None
+    with ck.Pool(g, w.seed, kv, max_claims=4 * claims, max_footprint=2 * refs,
+                 event_capacity=64 * claims + 64) as p:
+        slot = 0
+        for b in batches:
+            db = ck.DeviceBatch(b)
+            assert op.offload(b, d0) == O.OK
+            p.offload(db, staging=staging)
+            if staged:
+                ok = np.arange(b.num_claims)[np.diff(b.block_offsets.astype(np.int64)) >= 0]
+                seen = np.unique(np.concatenate([b.block_ids[b.block_offsets[c]:b.block_offsets[c + 1]]
+                                                 for c in ok]))
+                got = staging.cpu().numpy().reshape(-1, g.block_bytes)[slot:slot + seen.size]
+                want = host.reshape(g.planes, g.num_blocks, -1).transpose(1, 0, 2)[seen]
+                assert np.array_equal(got, want.reshape(seen.size, -1))
+                slot += seen.size
+            # the same ids again, one id twice in a batch: refused, nothing changes
+            with pytest.raises(ck.ClaimError) as e:
+                p.offload(db)
+            assert e.value.status == ck.EDUP
+        if claims > 1:
+            twice = family_batch(g, claims, blocks, rng, 300000)
+            twice[-1] = (twice[0][0],) + twice[-1][1:]
+            with pytest.raises(ck.ClaimError) as e:
+                p.offload(ck.DeviceBatch(from_claims(twice)))
+            assert e.value.status == ck.EDUP
+        assert p.identity_stats() == op.identity_stats()
+        for b in batches:
+            db = ck.DeviceBatch(b)
+            p.restore(db, staging=staging)
+            assert op.restore(b) == O.OK
+            p.check(db)
+            out = op.check(b, d0)
+        got, ev = p.read()
+        same_outcomes(got, out)
+        same_events(ev, op.events())
+        for b in batches:
+            lk, want = p.lookup(ck.DeviceBatch(b)), op.lookup(b)
+            for f in want.dtype.names:
+                if f != "pad":
+                    assert np.array_equal(lk[f], want[f]), f
+    del kv, staging
     free_gpu(torch)
