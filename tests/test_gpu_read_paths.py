@@ -22,9 +22,10 @@ def pinned(torch, dtype, n, shift=0):
     return mem, mem.numpy()[shift:].view(dtype)
 
 
-# 16-byte header and 64 + 40..80 bytes per claim: 64 KiB hold the bound of
+# 16-byte header and 64 + 40..80 bytes per claim (past 16 MiB the copies serve
+# page-locked memory too): 64 KiB hold the bound of
 # 455 claims (64 + 2 x 40 bytes each), not of 456
-@pytest.mark.parametrize("claims", [1, 454, 455, 456, 600, 1500, 20000])
+@pytest.mark.parametrize("claims", [1, 454, 455, 456, 600, 1500, 20000, 150000])
 def test_read_paths(torch, ck, claims):
     w = scaled(FULL["small-claim-stress"], 128, claims, corrupt_rate=0.05)
     batch = make_batch(w)
