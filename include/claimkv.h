@@ -455,11 +455,14 @@ int outcomes_read(claim_pool* pool, claim_outcome* out, uint32_t out_cap, uint32
  * workgroups of 4 waves; each wave reads one piece (64 lanes x
  * words_per_lane 8-byte words) of one plane's chunk of each block it
  * visits, a workgroup 4 consecutive pieces (a piece group), and the launch
- * reads pga piece groups at a time with groups workgroups on each. */
+ * reads pga piece groups at a time with groups workgroups on each.  Where
+ * no wide piece divides the chunk, a piece is 64 x words_per_lane
+ * consecutive words of the block's canonical bytes, across chunk ends
+ * (segments = 0). */
 typedef struct claim_grid_info {
   uint32_t words_per_lane;  /* 8-byte words per lane in one piece */
-  uint32_t segments;        /* pieces per plane chunk */
-  uint32_t piece_groups;    /* ceil(planes x segments / 4) */
+  uint32_t segments;        /* pieces per plane chunk; 0: pieces run across chunk ends */
+  uint32_t piece_groups;    /* ceil(pieces per block / 4) */
   uint32_t slots;           /* workgroups resident at once (per CU x CUs) */
   uint32_t pga;             /* a launch over `refs` entries: piece groups read at a time */
   uint32_t groups;          /* ... and workgroups on each */

@@ -12,7 +12,8 @@
 //    [plane][block][chunk].  D(b) = sum_i w_i k_i is linear in the words, so
 //    it splits into partial sums over pieces of the canonical block: a piece
 //    is one 64-lane x LPW 8-byte-word segment of a plane's chunk (LPW up to
-//    24 for whole chunks, 12 KiB; 32 for ragged ones), and since k_i depends
+//    24, 12 KiB) or, where none divides the chunk, a run of the canonical
+//    block's 512-byte rows across chunk ends; and since k_i depends
 //    only on the word's canonical position, a wave pinned to one piece keeps
 //    that piece's keys in VGPRs and streams the same piece of many blocks,
 //    with all LPW loads in flight before any use.  The 4 waves of a workgroup take 4 consecutive pieces
@@ -112,6 +113,12 @@ __device__ __forceinline__ uint32_t lane_read(uint32_t v, uint32_t src_lane) {
 __device__ __forceinline__ uint64_t uniform_read64(uint64_t v, uint32_t lane) {
   const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, lane);
   const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), lane);
+  return ((uint64_t)hi << 32) | lo;
+}
+
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
   return ((uint64_t)hi << 32) | lo;
 }
 
@@ -829,7 +836,6 @@ __device__ __forceinline__ uint64_t dpp_wave_sum64(uint64_t v) {
   return ((uint64_t)h << 32) | l;
 }
 
-// RAGGED: the chunk's last segment is partly past its end (masked slots).
 // STAGE: also copy the words to staging (offload with staging).
 // Position of a pool word in its block's full canonical bytes: the index of
 // its key.  A pool that holds every head has word q of plane p's chunk at
@@ -851,7 +857,7 @@ struct KeyMap {
   }
 };
 
-template <int LPW, bool RAGGED, bool STAGE>
+template <int LPW, bool STAGE>
 __global__ void __launch_bounds__(kThreads) k_digest(const u32x2* __restrict__ pool, uint32_t nb,
                                                      uint32_t chunk_words, uint32_t planes,
                                                      uint32_t segs, uint32_t pga, uint32_t groups,
@@ -878,30 +884,30 @@ __global__ void __launch_bounds__(kThreads) k_digest(const u32x2* __restrict__ p
     uint32_t klo[LPW], khi[LPW];
 #pragma unroll
     for (int k = 0; k < LPW; ++k) {
-      const uint32_t q = q0 + 64u * k;
-      const uint64_t key = stream_output(seed, km.at(p, q)) | 1ull;
-      const bool ok = !RAGGED || q < chunk_words;
-      klo[k] = ok ? (uint32_t)key : 0u;  // a masked slot contributes 0
-      khi[k] = ok ? (uint32_t)(key >> 32) : 0u;
+      const uint64_t key = stream_output(seed, km.at(p, q0 + 64u * k)) | 1ull;
+      klo[k] = (uint32_t)key;
+      khi[k] = (uint32_t)(key >> 32);
     }
 
     const u32x2* plane = pool + (uint64_t)p * nb * chunk_words;
     uint32_t n = 0;
+    // kAhead: the next block's id is loaded while a block is read.  Measured
+    // (MLA pool, 24 words): 126 blocks 54.6 -> 52.1 us, 6000 blocks the same;
+    // with 16 words the 8B pool read slower (126 blocks 43.9 -> 50.1 us, 8192
+    // 2323 -> 2355), so only the wide pieces do it.
+    constexpr bool kAhead = LPW > 16;
+    uint32_t id = kAhead && g < U ? uniq[g] : 0;
     for (uint32_t u = g; u < U; u += groups, ++n) {
       uint64_t sum = 0;
+      const uint32_t blk = kAhead ? id : uniq[u];
+      if constexpr (kAhead)
+        if (U - u > groups) id = uniq[u + groups];
       if (active) {
-        const u32x2* chunk = plane + (uint64_t)uniq[u] * chunk_words;
+        const u32x2* chunk = plane + (uint64_t)blk * chunk_words;
         const u32x2* lanep = chunk + q0;  // slot k at lanep + 64k: immediate offsets
         u32x2 x[LPW];
 #pragma unroll
-        for (int k = 0; k < LPW; ++k) {
-          // a masked slot reads the chunk's first word (its key is 0): no
-          // address outside the chunk is ever formed
-          if (!RAGGED || q0 + 64u * k < chunk_words)
-            x[k] = __builtin_nontemporal_load(lanep + 64 * k);
-          else
-            x[k] = __builtin_nontemporal_load(chunk);
-        }
+        for (int k = 0; k < LPW; ++k) x[k] = __builtin_nontemporal_load(lanep + 64 * k);
         __builtin_amdgcn_sched_barrier(0);  // every load in flight before any use
         uint64_t acc = 0;
         uint32_t cross = 0;
@@ -916,8 +922,121 @@ __global__ void __launch_bounds__(kThreads) k_digest(const u32x2* __restrict__ p
         if constexpr (STAGE) {
           u32x2* dst = staging + ((uint64_t)u * planes + p) * chunk_words + q0;
 #pragma unroll
+          for (int k = 0; k < LPW; ++k) dst[64 * k] = x[k];
+        }
+      }
+      const uint32_t slot = n % kRing;
+      if (lane == 0) ring[w][slot] = sum;
+      if (slot == kRing - 1 || u + groups >= U) {  // the same for all 4 waves
+        __syncthreads();
+        const uint32_t n0 = n - slot;
+        for (uint32_t i = threadIdx.x; i <= slot; i += kThreads)
+          partial[((uint64_t)pg * groups + g) * NW + n0 + i] =
+              ring[0][i] + ring[1][i] + ring[2][i] + ring[3][i];
+        __syncthreads();
+      }
+    }
+  }
+}
+
+// The same partials where no wide piece divides the chunk (a chunk of 9 or 36
+// rows of 512 bytes, or one that ends inside a row): a piece is LPW
+// consecutive 64-word rows of the block's canonical words i = p * CW + q,
+// running across chunk ends, so that every wave keeps up to 10 KiB in flight
+// and reduces it once whatever the chunk.  ROWS: the chunk is a whole number
+// of rows, so a row's plane is the same for the wave and its address is
+// scalar; else each lane keeps its words' own offsets.  Words past the
+// block's end (in the last piece) have key 0 and read the piece's first word.
+// Keys and offsets are made in a rolled loop through LDS: unrolled, their
+// code spilled scalar registers.  The next block's id is loaded while a block
+// is read: without that a 0.5 GB read took about 20 us longer wherever more
+// than 13 workgroups share a piece group (the ids' cache lines are then met
+// cold all the way).  Measured over 4 GB, GB/s, against pieces that divide
+// the chunk or mask its end: 9 rows in 61 planes 4505 -> 7071, 3 rows in 80
+// planes 4650 -> 6945, 10 rows 6477 -> 7019, 36 rows in 61 planes 6136 ->
+// 7084, 84 rows 6442 -> 7185; 13.5 rows 5954 -> 7005, 4.5 rows 4236 -> 6808,
+// 22.5 rows 7025 -> 7028, 31.5 rows 6992 -> 6996.
+template <int LPW, bool ROWS, bool STAGE>
+__global__ void __launch_bounds__(kThreads) k_digest_run(const u32x2* __restrict__ pool,
+                                                         uint32_t nb, uint32_t chunk_words,
+                                                         uint32_t planes, uint32_t ps_total,
+                                                         uint32_t pga, uint32_t groups,
+                                                         const uint32_t* __restrict__ uniq,
+                                                         const Counters* __restrict__ ctr,
+                                                         uint64_t seed, KeyMap km,
+                                                         uint64_t* __restrict__ partial,
+                                                         u32x2* __restrict__ staging) {
+  __shared__ uint64_t ring[kThreads / 64][kRing];
+  __shared__ uint64_t keys[kThreads / 64][64 * LPW], offs[kThreads / 64][64 * LPW];
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint64_t *own_keys = keys[w] + lane, *own_off = offs[w] + lane;
+  const uint32_t pgs = (ps_total + 3) / 4;
+  const uint32_t g = blockIdx.x / pga;
+  if (g >= groups) return;
+  const uint32_t U = ctr->uniq_count;
+  const uint32_t NW = (U + groups - 1) / groups;
+  const uint64_t block_words = (uint64_t)planes * chunk_words;
+  const uint64_t plane_words = (uint64_t)nb * chunk_words;
+  for (uint32_t pg = blockIdx.x % pga; pg < pgs; pg += pga) {  // one phase per piece group
+    const uint32_t ps = pg * 4 + w;
+    const bool active = ps < ps_total;  // wave-uniform: the last piece group may be short
+    const uint64_t i0 = (uint64_t)(active ? ps : 0) * 64 * LPW;
+    const uint64_t first = i0 / chunk_words * plane_words + i0 % chunk_words;
+
+    uint32_t klo[LPW], khi[LPW];
+    uint64_t off[LPW];  // ROWS: of the row's first word (scalar); else of the lane's word
+    uint32_t p = (uint32_t)(i0 / chunk_words);
+    uint64_t q = i0 - (uint64_t)p * chunk_words + (ROWS ? 0u : lane);
+    uint64_t plane = (uint64_t)p * plane_words;
+#pragma unroll 1
+    for (int k = 0; k < LPW; ++k) {
+      while (q >= chunk_words) {
+        q -= chunk_words;
+        ++p;
+        plane += plane_words;
+      }
+      const bool ok = p < planes;
+      own_off[64 * k] = ok ? plane + q : first;
+      own_keys[64 * k] =
+          ok ? stream_output(seed, km.at(p, (uint32_t)(ROWS ? q + lane : q))) | 1ull : 0ull;
+      q += 64;
+    }
+#pragma unroll
+    for (int k = 0; k < LPW; ++k) {
+      off[k] = own_off[64 * k];
+      if constexpr (ROWS) off[k] = uniform64(off[k]);
+      klo[k] = (uint32_t)own_keys[64 * k];
+      khi[k] = (uint32_t)(own_keys[64 * k] >> 32);
+    }
+
+    uint32_t n = 0;
+    uint32_t id = g < U ? uniq[g] : 0;
+    for (uint32_t u = g; u < U; u += groups, ++n) {
+      uint64_t sum = 0;
+      const u32x2* blk = pool + (uint64_t)id * chunk_words;
+      if (U - u > groups) id = uniq[u + groups];  // in flight while this block is read
+      if (active) {
+        u32x2 x[LPW];
+#pragma unroll
+        for (int k = 0; k < LPW; ++k) {
+          const u32x2* row = blk + off[k];
+          x[k] = __builtin_nontemporal_load(ROWS ? row + lane : row);
+        }
+        __builtin_amdgcn_sched_barrier(0);  // every load in flight before any use
+        uint64_t acc = 0;
+        uint32_t cross = 0;
+#pragma unroll
+        for (int k = 0; k < LPW; ++k) {
+          acc += (uint64_t)x[k].x * klo[k];
+          cross += x[k].x * khi[k] + x[k].y * klo[k];
+        }
+        sum = dpp_wave_sum64(acc + ((uint64_t)cross << 32));
+        if constexpr (STAGE) {
+          u32x2* dst = staging + (uint64_t)u * block_words + i0 + lane;
+#pragma unroll
           for (int k = 0; k < LPW; ++k)
-            if (!RAGGED || q0 + 64u * k < chunk_words) dst[64 * k] = x[k];
+            if (i0 + 64u * k + lane < block_words) dst[64 * k] = x[k];
         }
       }
       const uint32_t slot = n % kRing;
@@ -2663,39 +2782,55 @@ struct DigestGrid {
 template <int LPW>
 int launch_digest_lpw(claim_pool* P, DigestGrid gr, uint64_t* partial, void* staging,
                       int* wgs_per_cu) {
-  const uint32_t cw = (uint32_t)(2 * P->chunk_vecs);
-  const bool ragged = (uint64_t)P->segs * 64 * LPW != cw;
-  const void* fn;
-  if (ragged)
-    fn = staging ? (const void*)k_digest<LPW, true, true> : (const void*)k_digest<LPW, true, false>;
-  else
-    fn = staging ? (const void*)k_digest<LPW, false, true> : (const void*)k_digest<LPW, false, false>;
   if (wgs_per_cu)  // occupancy query only
-    return hip_status(hipOccupancyMaxActiveBlocksPerMultiprocessor(wgs_per_cu, fn, kThreads, 0));
-  const u32x2* pool = (const u32x2*)P->kv;
-  u32x2* st = (u32x2*)staging;
+    return hip_status(hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        wgs_per_cu, (const void*)k_digest<LPW, false>, kThreads, 0));
+  const uint32_t cw = (uint32_t)(2 * P->chunk_vecs);
   const dim3 grid(gr.pga * gr.groups), block(kThreads);
-#define GO(R, S)                                                                                \
-  hipLaunchKernelGGL((k_digest<LPW, R, S>), grid, block, 0, P->stream, pool, P->nb, cw, P->planes, \
-                     P->segs, gr.pga, gr.groups, P->uniq, P->ctr, P->seed, P->kmap, partial, st)
-  if (ragged) {
-    if (staging) GO(true, true); else GO(true, false);
-  } else {
-    if (staging) GO(false, true); else GO(false, false);
-  }
+#define GO(S)                                                                                     \
+  hipLaunchKernelGGL((k_digest<LPW, S>), grid, block, 0, P->stream, (const u32x2*)P->kv, P->nb,   \
+                     cw, P->planes, P->segs, gr.pga, gr.groups, P->uniq, P->ctr, P->seed,         \
+                     P->kmap, partial, (u32x2*)staging)
+  if (staging) GO(true); else GO(false);
 #undef GO
+  return hip_status(hipGetLastError());
+}
+
+template <int LPW, bool ROWS, bool STAGE>
+int launch_digest_run(claim_pool* P, DigestGrid gr, uint64_t* partial, void* staging,
+                      int* wgs_per_cu) {
+  if (wgs_per_cu)
+    return hip_status(hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        wgs_per_cu, (const void*)k_digest_run<LPW, ROWS, STAGE>, kThreads, 0));
+  hipLaunchKernelGGL((k_digest_run<LPW, ROWS, STAGE>), dim3(gr.pga * gr.groups),
+                     dim3(kThreads), 0, P->stream, (const u32x2*)P->kv, P->nb,
+                     (uint32_t)(2 * P->chunk_vecs), P->planes, P->ps_total, gr.pga, gr.groups,
+                     P->uniq, P->ctr, P->seed, P->kmap, partial, (u32x2*)staging);
   return hip_status(hipGetLastError());
 }
 
 // Launch the digest on grid gr (or, with wgs_per_cu, query its occupancy).
 int launch_digest(claim_pool* P, DigestGrid gr, uint64_t* partial, void* staging,
                   int* wgs_per_cu = nullptr) {
+  if (P->segs == 0) {  // pieces that run across chunk ends
+    const bool rows = P->chunk_vecs % 32 == 0;
+#define RUN_CASE(l)                                                                            \
+  if (P->lpw == l) {                                                                           \
+    if (rows)                                                                                  \
+      return staging ? launch_digest_run<l, true, true>(P, gr, partial, staging, wgs_per_cu)   \
+                     : launch_digest_run<l, true, false>(P, gr, partial, staging, wgs_per_cu); \
+    return staging ? launch_digest_run<l, false, true>(P, gr, partial, staging, wgs_per_cu)    \
+                   : launch_digest_run<l, false, false>(P, gr, partial, staging, wgs_per_cu);  \
+  }
+    RUN_CASE(1) RUN_CASE(2) RUN_CASE(4) RUN_CASE(8) RUN_CASE(20)
+#undef RUN_CASE
+    return CLAIM_EINVAL;
+  }
   switch (P->lpw) {
 #define DIGEST_CASE(l) \
   case l:              \
     return launch_digest_lpw<l>(P, gr, partial, staging, wgs_per_cu);
-    DIGEST_CASE(1) DIGEST_CASE(2) DIGEST_CASE(4) DIGEST_CASE(8) DIGEST_CASE(12) DIGEST_CASE(16)
-    DIGEST_CASE(24) DIGEST_CASE(32)
+    DIGEST_CASE(4) DIGEST_CASE(8) DIGEST_CASE(16) DIGEST_CASE(24)
 #undef DIGEST_CASE
     default:
       return CLAIM_EINVAL;
@@ -2776,20 +2911,26 @@ int append_events(claim_pool* P, const claim_batch* b, ClaimScratch sc, Counters
   } while (0)
 
 // Choose words per lane (LPW), segments per chunk and the digest grid.
-// LPW is the largest instantiated width of at most kMaxExactLpw words (24,
-// 16, 12, 8, ...) that divides the chunk's words-per-lane, so every segment
-// is full and each wave streams up to 12 KiB per block; chunks that are not
-// a whole number of 512-byte rows, or whose only exact widths are tiny, use
-// the smallest width covering the chunk (at most 32) with a ragged last
-// segment.  Measured on MI355X in one process over one allocation, two
-// repetitions each: 16 words (8 KiB pieces, 32 KiB in flight per CU)
-// instead of 32 (16 KiB pieces, 64 KiB) read the 8B pool 2.0 % faster
-// (7.32 TB/s), the stress pool 2.6 %, 64 KiB chunks 1.8 %, fp8 and 64-plane
-// 16 KiB pools 1.6-1.7 %, a 160-plane pool 0.8 %; the 70B pool 0.4 % and a
-// 128-plane 16 KiB pool 2.3 % slower.  The 36 KiB MLA chunk keeps 24 words
-// (12 words, 24 KiB in flight, read it 14 % slower).  The grid is
-// persistent and fully resident (no tail of late waves): slots = workgroups
-// per CU x CUs, shared by the piece groups read at a time (digest_grid).
+// LPW is 24, 16 or 8, the largest of them that divides the chunk's words per
+// lane (4 for chunks of 4, 20 or 28 rows), so every segment is full and each
+// wave streams up to 12 KiB per block.  Measured on MI355X in one process
+// over one allocation, two repetitions each: 16 words (8 KiB pieces, 32 KiB
+// in flight per CU) instead of 32 (16 KiB pieces, 64 KiB) read the 8B pool
+// 2.0 % faster (7.32 TB/s), the stress pool 2.6 %, 64 KiB chunks 1.8 %, fp8
+// and 64-plane 16 KiB pools 1.6-1.7 %, a 160-plane pool 0.8 %; the 70B pool
+// 0.4 % and a 128-plane 16 KiB pool 2.3 % slower.  The 36 KiB MLA chunk keeps
+// 24 words (12 words, 24 KiB in flight, read it 14 % slower).  Other chunks
+// take pieces that run across chunk ends (k_digest_run; segs = 0), of the
+// width that leaves the fewest rows of the last piece group empty.  Widths
+// measured there over 4 GB and 0.5 GB, GB/s: 9 rows in 61 planes, 20 words
+// 7049 and 6132, 16 words 6918 and 6119, 8 words 7039 and 6338, 4 words 6835
+// and 6199, 2 words 6431 and 5901, 1 word 4381 and 4137; chunks that end
+// inside a row (22.5 and 31.5 rows) 20 words 7017 and 6118, 7022 and 6122, 8
+// words 6859 and 6240, 6927 and 6333: those take 20 words in pools past
+// kWideRunBytes.  Chunks of 4 rows read the same either way (4 GB 6893 and
+// 6935, 0.5 GB 6357 and 6132 with 20 words).  The grid is persistent and
+// fully resident (no tail of late waves): slots = workgroups per CU x CUs,
+// shared by the piece groups read at a time (digest_grid).
 // Workgroups per CU: enough for about
 // kInflightPerCu bytes of loads in flight per CU (each wave keeps
 // LPW x 512 bytes in flight), at most what can be resident.  Measured on
@@ -2799,7 +2940,7 @@ int append_events(claim_pool* P, const claim_batch* b, ClaimScratch sc, Counters
 // 2.026 (2 per CU there), 70B unchanged (15.40 -> 15.43); more requests
 // outstanding than the memory needs only queue.
 constexpr int kInflightPerCu = 32 << 10;
-constexpr int kMaxExactLpw = 24;
+constexpr uint64_t kWideRunBytes = 2ull << 30;
 
 // The pool's page-locked memory for outcomes_read: past it the host's copy
 // (about 10 GB/s) costs more than finding out whether the caller's memory is
@@ -2812,25 +2953,38 @@ constexpr uint64_t kReadBytes = 64 << 10;
 constexpr uint64_t kDirectBytes = 16 << 20;
 
 int choose_digest_shape(claim_pool* P) {
-  static const int kLpw[] = {32, 24, 16, 12, 8, 4, 2, 1};  // instantiated widths, descending
   const uint64_t CW = 2 * P->chunk_vecs;  // 64-bit words per chunk
-  const uint64_t Q = (CW + 63) / 64;      // words per lane to cover one chunk
+  const uint64_t Q = CW / 64;             // whole rows of 64 words in one chunk
   int best = 0;
   if (CW % 64 == 0)
-    for (int d : kLpw)
-      if (d <= kMaxExactLpw && Q % d == 0) {
+    for (int d : {24, 16, 8, 4})
+      if (Q % d == 0 && (d >= 8 || Q <= 32)) {
         best = d;
         break;
       }
-  if (best && best < 8 && Q > 32) best = 0;  // only tiny exact widths: use a ragged tail
-  if (best == 0) {                           // ragged: the smallest width covering Q, at most 32
-    best = 32;
-    for (int d : kLpw)
-      if ((uint64_t)d >= Q) best = d;
+  if (best) {
+    P->segs = (uint32_t)(Q / best);
+    P->ps_total = P->planes * P->segs;
+  } else {
+    // pieces across chunk ends: the width whose padded rows cost least (pct:
+    // how much longer than the fastest each width takes per row)
+    const bool wide = CW % 64 != 0 && P->block_bytes * P->nb >= kWideRunBytes;
+    const struct { int lpw, pct; } kRun[] = {{8, wide ? 103 : 100}, {20, wide ? 100 : 102},
+                                             {4, 105}, {2, 115}, {1, 160}};
+    const uint64_t rows = (P->planes * CW + 63) / 64;
+    long double least = 0;
+    for (const auto& r : kRun) {
+      const uint64_t groups = (rows + 4 * r.lpw - 1) / (4 * r.lpw);
+      const long double cost = (long double)groups * (4 * r.lpw) * r.pct;
+      if (!best || cost < least) {
+        best = r.lpw;
+        least = cost;
+      }
+    }
+    P->segs = 0;
+    P->ps_total = (uint32_t)((rows + best - 1) / best);
   }
   P->lpw = best;
-  P->segs = (uint32_t)((Q + best - 1) / best);
-  P->ps_total = P->planes * P->segs;
   P->pgs = (P->ps_total + 3) / 4;
   int per_cu = 0;
   TRY(launch_digest(P, DigestGrid{1, 1}, nullptr, nullptr, &per_cu));  // the kernel's occupancy
@@ -2892,7 +3046,8 @@ DigestGrid digest_grid(const claim_pool* P, uint64_t refs) {
   const bool one = bytes <= (long double)kOnePhaseBytes;
   // two phases where half the piece groups end on a plane chunk's edge
   const bool two = one && bytes >= (long double)kTwoPhaseBytes && P->pgs % 2 == 0 &&
-                   (2ull * P->pgs) % P->segs == 0;
+                   (P->segs ? (2ull * P->pgs) % P->segs == 0
+                            : 2ull * P->pgs * 64 * P->lpw % (2 * P->chunk_vecs) == 0);
   for (uint32_t d = P->pgs; d >= 1; --d) {
     if (P->pgs % d || d > P->slots) continue;  // a phase must fit the resident slots
     if (d > 1 && !one && bytes * d > (long double)kPhaseBytes * P->pgs) continue;
