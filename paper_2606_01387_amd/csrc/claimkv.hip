@@ -3343,10 +3343,8 @@ constexpr uint64_t kAcceptFirst = 4096;
 // 40960 170.5 / 209.8.
 constexpr uint64_t kMergedRefs = 4096;
 
-namespace {
-
-int launch_admit_small(claim_pool* P, const claim_batch* b, DigestGrid gr, int staged,
-                       uint32_t slot0) {
+static int launch_admit_small(claim_pool* P, const claim_batch* b, DigestGrid gr, int staged,
+                              uint32_t slot0) {
   switch (group_width(b)) {
 #define ADMIT_CASE(w)                                                                             \
   case w:                                                                                         \
@@ -3368,8 +3366,6 @@ int launch_admit_small(claim_pool* P, const claim_batch* b, DigestGrid gr, int s
   }
   return hip_status(hipGetLastError());
 }
-
-}  // namespace
 
 int claim_offload(claim_pool* P, const claim_batch* b, void* staging, uint64_t staging_bytes) {
   if (!P || ((uintptr_t)staging & 15)) return CLAIM_EINVAL;
