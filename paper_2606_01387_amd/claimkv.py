@@ -253,7 +253,7 @@ class Pool:
         # needs them alive until that work completes, which the next call
         # that waits for the stream guarantees
         self._inflight = []
-        self._lookup_out = None
+        self._lookup_free = []  # page-locked result buffers no call is using
 
     def close(self) -> None:
         h = getattr(self, "_h", None)
@@ -261,7 +261,7 @@ class Pool:
             _check(lib().claim_pool_destroy(h), "claim_pool_destroy")
         self._h = None
         self._inflight = []
-        self._lookup_out = None
+        self._lookup_free = []
 
     def __del__(self):
         try:
@@ -346,17 +346,24 @@ class Pool:
             self.stream.synchronize()
             self._inflight = []
             return out.cpu().numpy().view(LOOKUP_DTYPE)[:n].copy()
-        # few results: the kernel writes them to page-locked memory (kept by
-        # the pool, at most LOOKUP_PINNED records), which saves the copy back
-        if self._lookup_out is None or self._lookup_out[0].numel() < n * LOOKUP_DTYPE.itemsize:
+        # few results: the kernel writes them to page-locked memory, which saves
+        # the copy back.  The pool keeps one buffer (at most LOOKUP_PINNED
+        # records); a call takes it out, so that another thread's call
+        # meanwhile gets one of its own
+        try:
+            mem = self._lookup_free.pop()
+        except IndexError:
+            mem = None
+        if mem is None or mem.numel() < n * LOOKUP_DTYPE.itemsize:
             mem = _torch().empty(max(64, n) * LOOKUP_DTYPE.itemsize, dtype=_torch().uint8,
                                  pin_memory=True)
-            self._lookup_out = (mem, mem.numpy().view(LOOKUP_DTYPE))
-        mem, records = self._lookup_out
         self.lookup_async(batch, out=mem)
         self.stream.synchronize()
         self._inflight = []
-        return records[:n].copy()
+        result = mem.numpy().view(LOOKUP_DTYPE)[:n].copy()
+        if not self._lookup_free:
+            self._lookup_free.append(mem)
+        return result
 
     def identity_stats(self) -> tuple[int, int]:
         """(registered identities, ambiguous identities)."""

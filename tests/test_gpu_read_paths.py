@@ -111,3 +111,29 @@ def test_lookup_paths(torch, ck, requests):
         assert np.array_equal(first, want)  # the first call's records are the caller's own
     del kv
     free_gpu(torch)
+
+
+def test_lookup_during_a_lookup(torch, ck):
+    """A lookup that another thread makes while one waits for its results
+    (here from within the call, after its launch) takes memory of its own."""
+    w = scaled(FULL["small-claim-stress"], 128, 300)
+    batch = make_batch(w)
+    reqs, _ = make_requests(w, batch, num_requests=100)
+    kv = gpu_pool_tensor(torch, w)
+    with ck.Pool(w.geometry, w.seed, kv) as p:
+        p.offload(ck.DeviceBatch(batch))
+        d, other = ck.DeviceBatch(reqs), ck.DeviceBatch(batch)
+        want, want_other = p.lookup(d), p.lookup(other)
+        assert not np.array_equal(want, want_other[: want.size])
+        queue, inner = p.lookup_async, []
+
+        def lookup_async(b, out=None):
+            queue(b, out)
+            if b is d:
+                inner.append(p.lookup(other))
+
+        p.lookup_async = lookup_async
+        assert np.array_equal(p.lookup(d), want)
+        assert np.array_equal(inner[0], want_other)
+    del kv
+    free_gpu(torch)
