@@ -297,13 +297,17 @@ static_assert(sizeof(Counters) == 72, "Counters layout");
 // them after one wait for the stream (a blit copy would be one more launch).
 // Every thread of the workgroup calls it.  The fence makes this workgroup's
 // own stores visible; the loads bypass the caches, since earlier atomics on
-// the line were performed past them.
+// the line were performed past them.  The host may read them after an event
+// alone, whose release need not reach past this device: the stores are
+// system-scope, and the host's copy is coherent memory.
 __device__ __forceinline__ void publish_counters(const Counters* ctr, Counters* host) {
   __threadfence();
   __syncthreads();
   if (threadIdx.x < sizeof(Counters) / 8)
-    ((uint64_t*)host)[threadIdx.x] = __hip_atomic_load((const uint64_t*)ctr + threadIdx.x,
-                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store((uint64_t*)host + threadIdx.x,
+                       __hip_atomic_load((const uint64_t*)ctr + threadIdx.x, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // call_pos of a call whose events do not fit the log: they are dropped, all
@@ -3274,7 +3278,8 @@ int claim_pool_create(const claim_pool_desc* d, claim_pool** out) {
     P->ev_cap = d->event_capacity;
     if ((rc = dalloc(&P->log, d->event_capacity))) break;
     if ((rc = dalloc(&P->ctr, 1))) break;
-    if (hipHostMalloc((void**)&P->host_ctr, sizeof(Counters), hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc((void**)&P->host_ctr, sizeof(Counters),
+                      hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
       P->host_ctr = nullptr;
       rc = CLAIM_ENOMEM;
       break;
