@@ -840,7 +840,18 @@ __device__ __forceinline__ uint64_t dpp_wave_sum64(uint64_t v) {
   return ((uint64_t)h << 32) | l;
 }
 
-// STAGE: also copy the words to staging (offload with staging).
+// STAGE: also copy the words to staging (offload with staging), past the
+// caches where the batch's blocks are many (kStageStreamBytes).
+enum StageMode : int { kNoStage = 0, kStageCached = 1, kStageStream = 2 };
+
+template <int STAGE>
+__device__ __forceinline__ void stage_store(u32x2* dst, u32x2 v) {
+  if constexpr (STAGE == kStageStream)
+    __builtin_nontemporal_store(v, dst);
+  else
+    *dst = v;
+}
+
 // Position of a pool word in its block's full canonical bytes: the index of
 // its key.  A pool that holds every head has word q of plane p's chunk at
 // p * chunk_words + q.  A head shard (tensor parallel by KV head) holds heads
@@ -861,7 +872,7 @@ struct KeyMap {
   }
 };
 
-template <int LPW, bool STAGE>
+template <int LPW, int STAGE>
 __global__ void __launch_bounds__(kThreads) k_digest(const u32x2* __restrict__ pool, uint32_t nb,
                                                      uint32_t chunk_words, uint32_t planes,
                                                      uint32_t segs, uint32_t pga, uint32_t groups,
@@ -923,10 +934,10 @@ __global__ void __launch_bounds__(kThreads) k_digest(const u32x2* __restrict__ p
           cross += x[k].x * khi[k] + x[k].y * klo[k];
         }
         sum = dpp_wave_sum64(acc + ((uint64_t)cross << 32));
-        if constexpr (STAGE) {
+        if constexpr (STAGE != kNoStage) {
           u32x2* dst = staging + ((uint64_t)u * planes + p) * chunk_words + q0;
 #pragma unroll
-          for (int k = 0; k < LPW; ++k) dst[64 * k] = x[k];
+          for (int k = 0; k < LPW; ++k) stage_store<STAGE>(dst + 64 * k, x[k]);
         }
       }
       const uint32_t slot = n % kRing;
@@ -960,7 +971,7 @@ __global__ void __launch_bounds__(kThreads) k_digest(const u32x2* __restrict__ p
 // planes 4650 -> 6945, 10 rows 6477 -> 7019, 36 rows in 61 planes 6136 ->
 // 7084, 84 rows 6442 -> 7185; 13.5 rows 5954 -> 7005, 4.5 rows 4236 -> 6808,
 // 22.5 rows 7025 -> 7028, 31.5 rows 6992 -> 6996.
-template <int LPW, bool ROWS, bool STAGE>
+template <int LPW, bool ROWS, int STAGE>
 __global__ void __launch_bounds__(kThreads) k_digest_run(const u32x2* __restrict__ pool,
                                                          uint32_t nb, uint32_t chunk_words,
                                                          uint32_t planes, uint32_t ps_total,
@@ -1036,11 +1047,11 @@ __global__ void __launch_bounds__(kThreads) k_digest_run(const u32x2* __restrict
           cross += x[k].x * khi[k] + x[k].y * klo[k];
         }
         sum = dpp_wave_sum64(acc + ((uint64_t)cross << 32));
-        if constexpr (STAGE) {
+        if constexpr (STAGE != kNoStage) {
           u32x2* dst = staging + (uint64_t)u * block_words + i0 + lane;
 #pragma unroll
           for (int k = 0; k < LPW; ++k)
-            if (i0 + 64u * k + lane < block_words) dst[64 * k] = x[k];
+            if (i0 + 64u * k + lane < block_words) stage_store<STAGE>(dst + 64 * k, x[k]);
         }
       }
       const uint32_t slot = n % kRing;
@@ -1591,13 +1602,62 @@ __global__ void __launch_bounds__(kThreads) k_set_failed(BlockRes* __restrict__ 
   if (f < n) bres[blocks[f]].fail_gen = gen;
 }
 
-// Copy staged blocks (those in the unique list) back into the pool.
+// Copy staged blocks (those in the unique list) back into the pool, a piece
+// of kUnstageVecs consecutive 16-byte words of one block's canonical bytes
+// per workgroup and step.  Bound by HBM reads and writes together (a copy
+// reaches about 5.1 TB/s): the block, its slot and the piece's plane are found
+// once per piece on the scalar unit, a thread's loads are all in flight before
+// its first store, and neither side is kept in the caches.  MLA pool, 13.5 GB
+// staged: 5470 us word by word, 5280 in pieces (4 loads per thread 5400, 12
+// 5465; 8 workgroups per CU 5335, 4 5325, 1 5240; stores kept in the caches
+// 5475).
+constexpr int kUnstageLoads = 8;
+constexpr uint32_t kUnstageVecs = kUnstageLoads * kThreads;
+
 __global__ void __launch_bounds__(kThreads) k_unstage(u32x4* __restrict__ pool, uint32_t nb,
                                                       uint32_t chunk_vecs, uint32_t planes,
                                                       const uint32_t* __restrict__ uniq,
                                                       const Counters* __restrict__ ctr,
                                                       const uint32_t* __restrict__ slot_of,
                                                       const u32x4* __restrict__ staging) {
+  const uint64_t per_block = (uint64_t)planes * chunk_vecs;
+  const uint64_t pieces = (per_block + kUnstageVecs - 1) / kUnstageVecs;
+  const uint64_t total = (uint64_t)ctr->uniq_count * pieces;
+  const uint64_t plane_vecs = (uint64_t)nb * chunk_vecs;
+  for (uint64_t i = blockIdx.x; i < total; i += gridDim.x) {
+    const uint64_t u = i / pieces, r0 = (i - u * pieces) * kUnstageVecs;
+    const uint32_t b = uniq[u];
+    const uint64_t p0 = r0 / chunk_vecs, v0 = r0 - p0 * chunk_vecs;
+    const uint64_t left = per_block - r0;  // words of the block from the piece's first
+    const u32x4* src = staging + (uint64_t)slot_of[b] * per_block + r0;
+    u32x4* dst = pool + p0 * plane_vecs + (uint64_t)b * chunk_vecs + v0;
+    u32x4 x[kUnstageLoads];
+#pragma unroll
+    for (int k = 0; k < kUnstageLoads; ++k) {
+      const uint32_t t = k * kThreads + threadIdx.x;
+      if (t < left) x[k] = __builtin_nontemporal_load(src + t);
+    }
+#pragma unroll
+    for (int k = 0; k < kUnstageLoads; ++k) {
+      const uint32_t t = k * kThreads + threadIdx.x;
+      if (t >= left) continue;
+      uint64_t off = t;
+      if (v0 + t >= chunk_vecs) {  // past the first plane's chunk, by less than a piece
+        const uint32_t over = (uint32_t)(v0 + t - chunk_vecs);
+        off += (1u + over / chunk_vecs) * (plane_vecs - chunk_vecs);
+      }
+      __builtin_nontemporal_store(x[k], dst + off);
+    }
+  }
+}
+
+// The same word by word (use_pieces says where).
+__global__ void __launch_bounds__(kThreads) k_unstage_words(u32x4* __restrict__ pool, uint32_t nb,
+                                                            uint32_t chunk_vecs, uint32_t planes,
+                                                            const uint32_t* __restrict__ uniq,
+                                                            const Counters* __restrict__ ctr,
+                                                            const uint32_t* __restrict__ slot_of,
+                                                            const u32x4* __restrict__ staging) {
   const uint64_t per_block = (uint64_t)planes * chunk_vecs;
   const uint64_t total = (uint64_t)ctr->uniq_count * per_block;
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -2777,6 +2837,35 @@ int select_blocks(claim_pool* P, const claim_batch* b, int mode, Counters* host 
   return hip_status(hipGetLastError());
 }
 
+// Whether a staged offload of up to refs blocks writes staging past the
+// caches: then the pool's reads keep more of the memory's time, but a restore
+// that follows finds nothing of a small staging buffer in the 256 MB last-level
+// cache.  Staged offload and restore, staging kept in the caches / not, us:
+// 0.26 GB 284 / 297, 0.32 GB 321 / 341, 0.42 GB 405 / 411, 0.52 GB 494 / 491,
+// 1.05 GB 887 / 879; the offload of 2.35 GB 1107 / 997, of 13.5 GB (MLA) 5477 /
+// 5230.
+constexpr uint64_t kStageStreamBytes = 448ull << 20;
+
+bool stream_stage(const claim_pool* P, uint64_t refs) {
+  return (long double)std::min<uint64_t>(refs, P->nb) * P->block_bytes >
+         (long double)kStageStreamBytes;
+}
+
+// Whether a restore of up to refs staged blocks copies them in pieces rather
+// than word by word.  Word by word / in pieces, us: 0.13 GB 61 / 69, 0.18-0.2 GB
+// 88-100 / 94-106 (the staged bytes are in the last-level cache, and more,
+// shorter workgroups hide its latency better), 0.26 GB 138 / 112, 0.52 GB 238 /
+// 225, 2 GB in 8 KiB chunks 804 / 784, in 16 KiB chunks 792 / 772, in 4 KiB
+// chunks (where a piece is 8 scattered runs) 798 / 799.  Blocks of fewer than 4
+// pieces would leave more than a quarter of the threads idle.
+constexpr uint64_t kPiecesBytes = 224ull << 20;
+constexpr uint64_t kPiecesChunk = 8 << 10;
+
+bool use_pieces(const claim_pool* P, uint64_t refs) {
+  return P->chunk_bytes >= kPiecesChunk && P->block_bytes >= 4 * 16 * kUnstageVecs &&
+         (long double)std::min<uint64_t>(refs, P->nb) * P->block_bytes > (long double)kPiecesBytes;
+}
+
 // The digest grid of one launch: pga piece groups read at a time, groups
 // workgroups on each (grid = pga x groups).
 struct DigestGrid {
@@ -2784,23 +2873,25 @@ struct DigestGrid {
 };
 
 template <int LPW>
-int launch_digest_lpw(claim_pool* P, DigestGrid gr, uint64_t* partial, void* staging,
+int launch_digest_lpw(claim_pool* P, DigestGrid gr, uint64_t refs, uint64_t* partial, void* staging,
                       int* wgs_per_cu) {
   if (wgs_per_cu)  // occupancy query only
     return hip_status(hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        wgs_per_cu, (const void*)k_digest<LPW, false>, kThreads, 0));
+        wgs_per_cu, (const void*)k_digest<LPW, kNoStage>, kThreads, 0));
   const uint32_t cw = (uint32_t)(2 * P->chunk_vecs);
   const dim3 grid(gr.pga * gr.groups), block(kThreads);
 #define GO(S)                                                                                     \
   hipLaunchKernelGGL((k_digest<LPW, S>), grid, block, 0, P->stream, (const u32x2*)P->kv, P->nb,   \
                      cw, P->planes, P->segs, gr.pga, gr.groups, P->uniq, P->ctr, P->seed,         \
                      P->kmap, partial, (u32x2*)staging)
-  if (staging) GO(true); else GO(false);
+  if (!staging) GO(kNoStage);
+  else if (stream_stage(P, refs)) GO(kStageStream);
+  else GO(kStageCached);
 #undef GO
   return hip_status(hipGetLastError());
 }
 
-template <int LPW, bool ROWS, bool STAGE>
+template <int LPW, bool ROWS, int STAGE>
 int launch_digest_run(claim_pool* P, DigestGrid gr, uint64_t* partial, void* staging,
                       int* wgs_per_cu) {
   if (wgs_per_cu)
@@ -2813,19 +2904,26 @@ int launch_digest_run(claim_pool* P, DigestGrid gr, uint64_t* partial, void* sta
   return hip_status(hipGetLastError());
 }
 
-// Launch the digest on grid gr (or, with wgs_per_cu, query its occupancy).
-int launch_digest(claim_pool* P, DigestGrid gr, uint64_t* partial, void* staging,
+template <int LPW, bool ROWS>
+int launch_digest_rows(claim_pool* P, DigestGrid gr, uint64_t refs, uint64_t* partial,
+                       void* staging, int* wgs_per_cu) {
+  if (!staging)
+    return launch_digest_run<LPW, ROWS, kNoStage>(P, gr, partial, staging, wgs_per_cu);
+  if (stream_stage(P, refs))
+    return launch_digest_run<LPW, ROWS, kStageStream>(P, gr, partial, staging, wgs_per_cu);
+  return launch_digest_run<LPW, ROWS, kStageCached>(P, gr, partial, staging, wgs_per_cu);
+}
+
+// Launch the digest of up to refs blocks on grid gr (or, with wgs_per_cu,
+// query its occupancy).
+int launch_digest(claim_pool* P, DigestGrid gr, uint64_t refs, uint64_t* partial, void* staging,
                   int* wgs_per_cu = nullptr) {
   if (P->segs == 0) {  // pieces that run across chunk ends
     const bool rows = P->chunk_vecs % 32 == 0;
-#define RUN_CASE(l)                                                                            \
-  if (P->lpw == l) {                                                                           \
-    if (rows)                                                                                  \
-      return staging ? launch_digest_run<l, true, true>(P, gr, partial, staging, wgs_per_cu)   \
-                     : launch_digest_run<l, true, false>(P, gr, partial, staging, wgs_per_cu); \
-    return staging ? launch_digest_run<l, false, true>(P, gr, partial, staging, wgs_per_cu)    \
-                   : launch_digest_run<l, false, false>(P, gr, partial, staging, wgs_per_cu);  \
-  }
+#define RUN_CASE(l)                                                                    \
+  if (P->lpw == l)                                                                     \
+    return rows ? launch_digest_rows<l, true>(P, gr, refs, partial, staging, wgs_per_cu) \
+                : launch_digest_rows<l, false>(P, gr, refs, partial, staging, wgs_per_cu);
     RUN_CASE(1) RUN_CASE(2) RUN_CASE(4) RUN_CASE(8) RUN_CASE(20)
 #undef RUN_CASE
     return CLAIM_EINVAL;
@@ -2833,7 +2931,7 @@ int launch_digest(claim_pool* P, DigestGrid gr, uint64_t* partial, void* staging
   switch (P->lpw) {
 #define DIGEST_CASE(l) \
   case l:              \
-    return launch_digest_lpw<l>(P, gr, partial, staging, wgs_per_cu);
+    return launch_digest_lpw<l>(P, gr, refs, partial, staging, wgs_per_cu);
     DIGEST_CASE(4) DIGEST_CASE(8) DIGEST_CASE(16) DIGEST_CASE(24)
 #undef DIGEST_CASE
     default:
@@ -2991,7 +3089,7 @@ int choose_digest_shape(claim_pool* P) {
   P->lpw = best;
   P->pgs = (P->ps_total + 3) / 4;
   int per_cu = 0;
-  TRY(launch_digest(P, DigestGrid{1, 1}, nullptr, nullptr, &per_cu));  // the kernel's occupancy
+  TRY(launch_digest(P, DigestGrid{1, 1}, 0, nullptr, nullptr, &per_cu));  // the kernel's occupancy
   const int wg_bytes = 4 * best * 64 * 8;  // loads in flight per workgroup
   const int want = kInflightPerCu / wg_bytes > 1 ? kInflightPerCu / wg_bytes : 1;
   if (per_cu > want) per_cu = want;
@@ -3404,7 +3502,7 @@ int claim_offload(claim_pool* P, const claim_batch* b, void* staging, uint64_t s
   // launches after it hide behind it.
   HIP_TRY(hipEventRecord(P->verdict, P->stream));
   const DigestGrid gr = digest_grid(P, b->num_refs);
-  if (!staging) TRY(launch_digest(P, gr, P->partial, nullptr));
+  if (!staging) TRY(launch_digest(P, gr, b->num_refs, P->partial, nullptr));
   HIP_TRY(hipEventSynchronize(P->verdict));  // the kernels published the counters
   if (P->host_ctr->dup_flag & kFlagDupId) {
     HIP_TRY(hipStreamSynchronize(P->stream));  // a refused call leaves nothing running
@@ -3442,7 +3540,7 @@ int claim_offload(claim_pool* P, const claim_batch* b, void* staging, uint64_t s
   P->gen += 1;
   if (staging && !append) TRY(fill<uint32_t>(P, P->slot_of, P->nb, kNone));
   if (staging)
-    TRY(launch_digest(P, gr, P->partial, (uint8_t*)staging + slot0 * P->block_bytes));
+    TRY(launch_digest(P, gr, b->num_refs, P->partial, (uint8_t*)staging + slot0 * P->block_bytes));
   if (!fpo && check_is_small(P, b)) {
     TRY(launch_admit_small(P, b, gr, staging != nullptr, (uint32_t)slot0));
   } else {
@@ -3519,9 +3617,18 @@ int claim_restore(claim_pool* P, const claim_batch* b, const void* staging,
 
   if (staging) {
     TRY(select_blocks(P, b, kMarkStaged));
-    hipLaunchKernelGGL(k_unstage, dim3(grid_for((uint64_t)P->nb * P->planes * P->chunk_vecs, 65536)),
-                       dim3(kThreads), 0, P->stream, (u32x4*)P->kv, P->nb, (uint32_t)P->chunk_vecs,
-                       P->planes, P->uniq, P->ctr, P->slot_of, (const u32x4*)staging);
+    const uint64_t block_vecs = P->planes * P->chunk_vecs;
+    if (use_pieces(P, b->num_refs)) {
+      const uint64_t pieces = (block_vecs + kUnstageVecs - 1) / kUnstageVecs;
+      const uint64_t most = std::min<uint64_t>(P->nb, b->num_refs) * pieces;
+      hipLaunchKernelGGL(k_unstage, dim3((uint32_t)std::min<uint64_t>(most, 2 * P->cus)), dim3(kThreads), 0, P->stream, (u32x4*)P->kv, P->nb,
+                         (uint32_t)P->chunk_vecs, P->planes, P->uniq, P->ctr, P->slot_of,
+                         (const u32x4*)staging);
+    } else {
+      hipLaunchKernelGGL(k_unstage_words, dim3(grid_for(P->nb * block_vecs, 65536)), dim3(kThreads),
+                         0, P->stream, (u32x4*)P->kv, P->nb, (uint32_t)P->chunk_vecs, P->planes,
+                         P->uniq, P->ctr, P->slot_of, (const u32x4*)staging);
+    }
     HIP_TRY(hipGetLastError());
   }
   const uint64_t need = nflip > nfail ? nflip : nfail;
@@ -3607,7 +3714,7 @@ int check_body(claim_pool* P, const claim_batch* b, claim_outcome* out, ClaimScr
   TRY(select_blocks(P, b, kMarkOffloaded));  // recorded blocks of the well-formed rows
   TRY(record_stage(P, slot, 1));
   const DigestGrid gr = digest_grid(P, b->num_refs);
-  TRY(launch_digest(P, gr, P->partial, nullptr));
+  TRY(launch_digest(P, gr, b->num_refs, P->partial, nullptr));
   TRY(record_stage(P, slot, 2));
   CheckState st;
   st.bres = P->bres;

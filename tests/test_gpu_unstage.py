@@ -1,0 +1,65 @@
+"""Staged blocks return to the pool in pieces of 2048 16-byte words of a block
+where the batch, its blocks and their chunks are large enough, word by word
+otherwise; large staged offloads write past the caches.  Sizes on both sides
+of each line, pieces that end inside a chunk and cross chunk ends, and every
+kind of digest piece: staging must hold the blocks' bytes, every restored
+block its bytes again, in whatever order its claims stage and restore it, and
+every other block must stay untouched."""
+
+import numpy as np
+import pytest
+
+from paper_2606_01387_amd.synth import TINY, Geometry, Workload, from_claims
+from tests.test_gpu_parity import free_gpu, gpu_pool_tensor, note
+
+pytestmark = pytest.mark.gpu
+
+# layers, planes per layer, block size, heads, dim, element bytes, blocks
+CASES = [
+    Geometry(1, 1, 2, 1, 8, 1, 300),  # blocks of one word
+    Geometry(1025, 1, 2, 1, 8, 1, 40),  # 16-byte chunks
+    Geometry(7, 1, 64, 1, 576, 1, 60),  # few bytes
+    Geometry(8, 2, 1, 1, 8176, 1, 1900),  # chunks just under 8 KiB
+    Geometry(15, 1, 16, 1, 256, 2, 2000),  # blocks of just under 4 pieces
+    Geometry(8, 2, 16, 1, 256, 2, 1900),  # 4 whole chunks a piece, 4 pieces a block
+    Geometry(17, 1, 1, 1, 8208, 1, 1800),  # chunks of 513 words
+    Geometry(1, 1, 1, 1, 524304, 1, 470),  # one chunk of 16 pieces and a word
+    Geometry(7, 1, 64, 1, 576, 1, 980),  # 36 KiB chunks
+    # past 448 MiB: each kind of digest piece stores its stream
+    Geometry(32, 2, 16, 8, 128, 2, 240),
+    Geometry(61, 1, 64, 1, 576, 1, 230),
+    Geometry(80, 2, 16, 1, 128, 2, 760),
+    Geometry(61, 1, 8, 1, 576, 1, 1750),
+    Geometry(17, 2, 24, 3, 80, 2, 1260),
+]
+
+
+@pytest.mark.parametrize("g", CASES, ids=[f"{g.chunk_bytes}Bx{g.planes}x{g.num_blocks}" for g in CASES])
+def test_unstage(torch, ck, g):
+    rng = np.random.default_rng(g.chunk_bytes + g.planes)
+    w = Workload(name="unstage", geometry=g, seed=5, num_claims=0, length=TINY.length,
+                 sharing=TINY.sharing, corrupt_rate=0.0, gen_seed=1, content_seed=7)
+    note(f"unstage {g.chunk_bytes} B x {g.planes} planes, {g.num_blocks} blocks")
+    kv = gpu_pool_tensor(torch, w)
+    pool = kv.view(g.planes, g.num_blocks, g.chunk_bytes)
+    want = pool.clone()
+    order = rng.permutation(g.num_blocks)[: g.num_blocks - 3]
+    claims = [(i + 1, [int(b)], rng.integers(0, 32000, g.block_size)) for i, b in enumerate(order)]
+    batch, part = from_claims(claims), from_claims([claims[4], claims[0]])
+    staging = torch.zeros(order.size * g.block_bytes, dtype=torch.uint8, device="cuda")
+    with ck.Pool(g, w.seed, kv, max_claims=4096, max_footprint=4096, event_capacity=32768) as p:
+        p.offload(ck.DeviceBatch(batch), staging=staging)
+        used = torch.from_numpy(np.sort(order)).cuda()
+        rows = staging.view(order.size, g.planes, g.chunk_bytes)
+        assert all(torch.equal(rows[:, l], want[l, used]) for l in range(g.planes))
+        for b, blocks in ((part, order[[4, 0]]), (from_claims([]), order[:0]), (batch, order)):
+            pool.fill_(0x5A)
+            p.restore(ck.DeviceBatch(b), staging=staging)
+            torch.cuda.synchronize()
+            back = torch.zeros(g.num_blocks, dtype=torch.bool, device="cuda")
+            back[torch.from_numpy(blocks).cuda()] = True
+            for l in range(g.planes):
+                assert torch.equal(pool[l, back], want[l, back])
+                assert bool((pool[l, ~back] == 0x5A).all())
+    del kv, pool, want, staging, rows
+    free_gpu(torch)
