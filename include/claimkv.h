@@ -332,9 +332,10 @@ int claim_pool_destroy(claim_pool* pool);
  * as the pool holds it (a claim whose bytes are gone fails closed on its
  * digest compare), although lookups may still hit its identity.  Stores
  * are not deduplicated across calls: a block staged again takes a new slot.
- * Waits twice
- * for the stream to read the acceptance verdict (three times when a block
- * row runs backwards).  ENOSPC if the registry, footprint store or event
+ * Waits
+ * for the acceptance verdict, then for the stream (and once more between
+ * them when a block row runs backwards); a refused call reads no block and
+ * waits for the verdict alone.  ENOSPC if the registry, footprint store or event
  * log could overflow; the footprint store takes num_refs entries, or, when
  * rows share entries, the sum of the well-formed rows' lengths.
  */

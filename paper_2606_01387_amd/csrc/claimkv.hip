@@ -310,6 +310,18 @@ __device__ __forceinline__ void publish_counters(const Counters* ctr, Counters* 
                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// An offload's verdict for the host: the counters as they are.  A batch that
+// the host will refuse, or whose rows may share entries, then has no blocks
+// for a digest queued ahead of the host's answer, which ends at once: a
+// refusal of 1024 claims over the whole 8B pool takes 42 us until the stream
+// is idle, and took 2356 us while the digest read the blocks.
+// Every thread of the workgroup calls it.
+__device__ __forceinline__ void publish_verdict(Counters* ctr, Counters* host) {
+  publish_counters(ctr, host);
+  // the thread that clears the count is the one that has published it
+  if (threadIdx.x == 0 && ctr->dup_flag) ctr->uniq_count = 0;
+}
+
 // call_pos of a call whose events do not fit the log: they are dropped, all
 // of them, and log_dropped is set.  The host bounds every call it queues
 // itself; the device bound keeps the log in bounds for work the host cannot
@@ -751,7 +763,7 @@ __global__ void __launch_bounds__(1024) k_select_small(BatchDev b, uint32_t lg, 
 // read as one 8-byte word (the mark array is padded to a multiple of 16
 // bytes with zeros); a step's indices are gathered in LDS and written out
 // with coalesced stores; clears the marks it reads.  With `host` it then
-// publishes the counters (an offload's verdict).
+// publishes an offload's verdict.
 __global__ void __launch_bounds__(1024) k_compact(uint8_t* __restrict__ mark, uint32_t nb,
                                                   uint32_t* __restrict__ uniq, Counters* ctr,
                                                   Counters* host) {
@@ -782,7 +794,7 @@ __global__ void __launch_bounds__(1024) k_compact(uint8_t* __restrict__ mark, ui
     __syncthreads();
   }
   if (threadIdx.x == 0) ctr->uniq_count = base;
-  if (host) publish_counters(ctr, host);
+  if (host) publish_verdict(ctr, host);
 }
 
 // ----------------------------------------------------------- digest kernel
@@ -887,8 +899,8 @@ __global__ void __launch_bounds__(kThreads) k_digest(const u32x2* __restrict__ p
   const uint32_t ps_total = planes * segs;
   const uint32_t pgs = (ps_total + 3) / 4;
   const uint32_t g = blockIdx.x / pga;
-  if (g >= groups) return;
   const uint32_t U = ctr->uniq_count;
+  if (g >= groups || g >= U) return;  // no block of its own: no keys either
   const uint32_t NW = (U + groups - 1) / groups;
   for (uint32_t pg = blockIdx.x % pga; pg < pgs; pg += pga) {  // one phase per piece group
     const uint32_t ps = pg * 4 + w;
@@ -988,8 +1000,8 @@ __global__ void __launch_bounds__(kThreads) k_digest_run(const u32x2* __restrict
   uint64_t *own_keys = keys[w] + lane, *own_off = offs[w] + lane;
   const uint32_t pgs = (ps_total + 3) / 4;
   const uint32_t g = blockIdx.x / pga;
-  if (g >= groups) return;
   const uint32_t U = ctr->uniq_count;
+  if (g >= groups || g >= U) return;  // no block of its own: no keys either
   const uint32_t NW = (U + groups - 1) / groups;
   const uint64_t block_words = (uint64_t)planes * chunk_words;
   const uint64_t plane_words = (uint64_t)nb * chunk_words;
@@ -1209,9 +1221,11 @@ __global__ void __launch_bounds__(kThreads) k_dup_clear(unsigned long long* __re
 // runs backwards): each well-formed claim gets a run of its own in the
 // footprint and identity stores, at fp_base plus the exclusive prefix sum of
 // the row lengths in claim order (a malformed row takes none); fpo[C] is the
-// total.  One workgroup; only such batches pay for it.
+// total.  It also gives the selection its count of unique blocks back, which
+// the verdict cleared.  One workgroup; only such batches pay for it.
 __global__ void __launch_bounds__(1024) k_footprint_offsets(BatchDev b, uint64_t fp_base,
-                                                            uint64_t* __restrict__ fpo) {
+                                                            uint64_t* __restrict__ fpo,
+                                                            uint32_t uniq_count, Counters* ctr) {
   __shared__ uint64_t s_sum[1024];
   const uint32_t t = threadIdx.x;
   const uint64_t per = (b.C + 1023) / 1024;
@@ -1233,6 +1247,7 @@ __global__ void __launch_bounds__(1024) k_footprint_offsets(BatchDev b, uint64_t
     at += read_row(b, c).n;
   }
   if (t == 1023) fpo[b.C] = s_sum[1023];
+  if (t == 0) ctr->uniq_count = uniq_count;
 }
 
 // Acceptance: chain hash of the claim's tokens, presence of its footprint
@@ -1531,7 +1546,7 @@ __global__ void __launch_bounds__(1024) k_admit_select(BatchDev b, RegDev reg, u
   }
   select_small(b, lg, nb, kMarkAny, nullptr, nullptr, bits, scan, uniq, ctr);
   if (t == 0) ctr->dup_flag = flags;  // select_small's barriers ordered the flags
-  publish_counters(ctr, host);
+  publish_verdict(ctr, host);
 }
 
 // The rest of a small offload in one workgroup, after its digest: the
@@ -3499,15 +3514,17 @@ int claim_offload(claim_pool* P, const claim_batch* b, void* staging, uint64_t s
   }
   // The host waits for the verdict alone.  Without staging the digest (it
   // writes only scratch) is queued before the wait, so that the wait and the
-  // launches after it hide behind it.
+  // launches after it hide behind it.  A batch that may be refused for its
+  // ids or whose rows may share entries gives it no blocks
+  // (publish_verdict), and one of disjoint rows whose footprint does not fit
+  // is refused below whatever the verdict: it has none queued.
   HIP_TRY(hipEventRecord(P->verdict, P->stream));
   const DigestGrid gr = digest_grid(P, b->num_refs);
-  if (!staging) TRY(launch_digest(P, gr, b->num_refs, P->partial, nullptr));
+  const bool ahead = !staging && P->fp_used + b->num_refs <= P->max_fp;
+  if (ahead) TRY(launch_digest(P, gr, b->num_refs, P->partial, nullptr));
   HIP_TRY(hipEventSynchronize(P->verdict));  // the kernels published the counters
-  if (P->host_ctr->dup_flag & kFlagDupId) {
-    HIP_TRY(hipStreamSynchronize(P->stream));  // a refused call leaves nothing running
-    return CLAIM_EDUP;
-  }
+  // (what is still queued has no blocks: it reads nothing of the caller's)
+  if (P->host_ctr->dup_flag & kFlagDupId) return CLAIM_EDUP;
   const uint64_t U = P->host_ctr->uniq_count;
   // staging into the current generation's buffer appends after its slots;
   // any other buffer starts a new generation
@@ -3521,17 +3538,14 @@ int claim_offload(claim_pool* P, const claim_batch* b, void* staging, uint64_t s
   uint64_t fp_need = b->num_refs;
   if (P->host_ctr->dup_flag & kFlagBackwardRow) {
     hipLaunchKernelGGL(k_footprint_offsets, dim3(1), dim3(1024), 0, P->stream, bd, P->fp_used,
-                       P->fpo);
+                       P->fpo, (uint32_t)U, P->ctr);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipMemcpyAsync(&fp_need, P->fpo + C, sizeof(uint64_t), hipMemcpyDeviceToHost,
                            P->stream));
     HIP_TRY(hipStreamSynchronize(P->stream));
     fpo = P->fpo;
   }
-  if (P->fp_used + fp_need > P->max_fp) {  // nothing changed
-    HIP_TRY(hipStreamSynchronize(P->stream));
-    return CLAIM_ENOSPC;
-  }
+  if (P->fp_used + fp_need > P->max_fp) return CLAIM_ENOSPC;  // nothing changed or running
 
   // the offload digest of every block the batch references (staged from
   // slot slot0 of the current generation's buffer; another buffer starts a
@@ -3541,6 +3555,8 @@ int claim_offload(claim_pool* P, const claim_batch* b, void* staging, uint64_t s
   if (staging && !append) TRY(fill<uint32_t>(P, P->slot_of, P->nb, kNone));
   if (staging)
     TRY(launch_digest(P, gr, b->num_refs, P->partial, (uint8_t*)staging + slot0 * P->block_bytes));
+  else if (fpo)  // not with the verdict
+    TRY(launch_digest(P, gr, b->num_refs, P->partial, nullptr));
   if (!fpo && check_is_small(P, b)) {
     TRY(launch_admit_small(P, b, gr, staging != nullptr, (uint32_t)slot0));
   } else {
