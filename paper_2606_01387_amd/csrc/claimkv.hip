@@ -2803,12 +2803,26 @@ bool select_is_small(const claim_pool* P, const claim_batch* b) {
 }
 
 // An offload's front (duplicate check and selection): the host waits for its
-// verdict, so its launches count whole.
+// verdict, so its launches count whole.  One CU walks every position and two
+// launches fewer read the pool's marks, so the line rises with the pool.
+// Measured, one offload (separate launches / one workgroup, us):
+//   8192 blocks    16 claims of 32 / 512 / 1024 68 / 62, 191 / 189, 298 / 289;
+//                  64 of 64 / 128 / 256 / 2048 blocks 80 / 77, 106 / 101,
+//                  132 / 137, 549 / 596; 128 of 32 / 64 / 128 / 2048 78 / 75,
+//                  91 / 89, 106 / 109, 574 / 665; 1024 of 4 / 8 84 / 78, 96 / 94
+//   65536 blocks   64 claims of 64 / 192 / 512 blocks 93 / 77, 123 / 112, 205 /
+//                  216; 128 of 64 / 96 / 256 100 / 84, 104 / 97, 153 / 163
+//   262144 blocks  64 claims of 192 / 512 / 1024 blocks 156 / 112, 239 / 220,
+//                  380 / 375; 128 of 64 / 256 / 512 132 / 84, 185 / 161, 266 / 267
+// Up to kSelectLanes every claim has its lanes at once, and the selection's
+// own rule holds.
 constexpr uint64_t kFrontLanes = 8192;  // C x W
+constexpr uint64_t kFrontRefs = 8192;   // and one position for 8 blocks of the pool
 
 bool front_is_small(const claim_pool* P, const claim_batch* b) {
   return P->nb <= kSelectBlocks && b->num_claims <= kFrontClaims &&
-         (uint64_t)b->num_claims * group_width(b) <= kFrontLanes;
+         (uint64_t)b->num_claims * group_width(b) <= kFrontLanes &&
+         (b->num_refs <= kFrontRefs + P->nb / 8 || select_is_small(P, b));
 }
 
 bool check_is_small(const claim_pool* P, const claim_batch* b) {

@@ -102,10 +102,11 @@ def test_small_batch(torch, ck, pool, claims, blocks):
     free_gpu(torch)
 
 
-# the front's edges: claims 1024 and past, lanes (claims x width) 8192 and past;
-# the tail's: as above
+# the front's edges: claims 1024 and past, lanes (claims x width) 8192 and past,
+# 8229 positions and past (8192 and one for 8 of the 300 blocks) where claims
+# have more than 1024 lanes; the tail's: as above
 FRONT = [(1, 3), (16, 64), (17, 64), (32, 20), (33, 20), (128, 64), (129, 64), (512, 2), (513, 2),
-         (1024, 4), (1024, 9), (1025, 1)]
+         (1024, 4), (1024, 9), (1025, 1), (128, 66), (24, 340), (24, 512), (16, 1000)]
 
 
 def family_batch(g, claims, blocks, rng, base, first=None):
