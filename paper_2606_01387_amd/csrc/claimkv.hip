@@ -2782,13 +2782,22 @@ int ensure_claim_scratch(claim_pool* P, uint64_t C, bool for_check) {
 // several it is split over otherwise: a launch behind another costs about
 // 2.5 us beside its work, and 3-4 us of host time.
 //
-// Selection: the claims in one round of 1024 lanes, and a pool whose bitmap
-// takes at most 32 KiB of LDS.  Measured against k_mark and k_compact: one
-// check waited for 0.6-2.4 us shorter up to 1024 lanes, checks queued behind
-// each other the same; 2048 lanes 0.5 us shorter and 0.5 us longer, 4096
-// lanes 2 us longer both ways.
+// Selection: the claims in one round of 1024 lanes, a pool whose bitmap takes
+// at most 32 KiB of LDS, and at most kSelectListed blocks to list, and one for
+// 8 blocks of the pool (a thread lists its share of the bitmap one store after
+// another; k_compact reads every mark of the pool), unless the claims are so
+// few that k_mark is one workgroup too.  Measured against k_mark and
+// k_compact: one check waited for 0.6-2.4 us shorter up to 1024 lanes, checks
+// queued behind each other the same; 2048 lanes 0.5 us shorter and 0.5 us
+// longer, 4096 lanes 2 us longer both ways.  Long rows (separate / one
+// workgroup, us): 262144 blocks, 16 claims of 2048 / 4104 / 6000 / 8192 165 / 118,
+// 258 / 232, 337 / 337, 431 / 446, 4 of 16384 689 / 601, 1 of 65536 2036 / 1842;
+// 100000 blocks, 16 of 4096 / 4104 / 6000 218 / 204, 218 / 218, 296 / 316, 4 of
+// 32768 1176 / 1063; 65536 and 8192 blocks, 16 of 8192 330 / 305, 243 / 219.
 constexpr uint64_t kSelectLanes = 1024;  // C x W
 constexpr uint32_t kSelectBlocks = 32768 * 8;
+constexpr uint64_t kSelectListed = 65536;
+constexpr uint32_t kOneGroupClaims = kThreads / 64;  // one workgroup at any width
 // Tail: the claims in one round of 1024 lanes, at most kTailRefs positions
 // (one CU hashes them) and kTailPartials partials (one CU reads them).
 // Measured, one check waited for (separate launches -> k_check_small): 64
@@ -2799,7 +2808,9 @@ constexpr uint32_t kSelectBlocks = 32768 * 8;
 constexpr uint64_t kTailRefs = 1024, kTailPartials = 32768;
 
 bool select_is_small(const claim_pool* P, const claim_batch* b) {
-  return P->nb <= kSelectBlocks && (uint64_t)b->num_claims * group_width(b) <= kSelectLanes;
+  return P->nb <= kSelectBlocks && (uint64_t)b->num_claims * group_width(b) <= kSelectLanes &&
+         (b->num_claims <= kOneGroupClaims ||
+          std::min<uint64_t>(b->num_refs, P->nb) <= kSelectListed + P->nb / 8);
 }
 
 // An offload's front (duplicate check and selection): the host waits for its

@@ -1,4 +1,5 @@
-"""Small batches take one-workgroup kernels: the selection (up to 1024 lanes),
+"""Small batches take one-workgroup kernels: the selection (up to 1024 lanes,
+and 65536 blocks to list, one more for 8 of the pool, for more than 4 claims),
 the restore (up to 1024 claims) and the check's tail (up to 1024 lanes and
 positions, 32768 partials); larger ones the kernels split over workgroups.
 At and around those edges both must give the oracle's digests, outcomes and
@@ -48,9 +49,11 @@ def small_batch(g, claims, blocks, rng):
     return b
 
 
-# the large pools repeat three batches
+# the large pools repeat three batches, and one lists many blocks on both sides
+# of the line
 CASES = [(p, c, n) for p in POOLS for c, n in BATCHES
          if POOLS[p].num_blocks < 2000 or (c, n) in ((1, 200), (32, 32), (33, 32))]
+CASES += [("bitmap-full", 16, 6140), ("bitmap-full", 16, 6160), ("bitmap-full", 4, 25000)]
 
 
 @pytest.mark.parametrize("pool,claims,blocks", CASES, ids=[f"{p}-{c}x{n}" for p, c, n in CASES])
