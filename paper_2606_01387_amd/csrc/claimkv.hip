@@ -2798,14 +2798,28 @@ constexpr uint64_t kSelectLanes = 1024;  // C x W
 constexpr uint32_t kSelectBlocks = 32768 * 8;
 constexpr uint64_t kSelectListed = 65536;
 constexpr uint32_t kOneGroupClaims = kThreads / 64;  // one workgroup at any width
-// Tail: the claims in one round of 1024 lanes, at most kTailRefs positions
-// (one CU hashes them) and kTailPartials partials (one CU reads them).
-// Measured, one check waited for (separate launches -> k_check_small): 64
-// piece groups, 8 / 128 / 256 / 512 / 1024 blocks 32.6 -> 27.3, 67.8 ->
-// 63.1, 106 -> 102, 183 -> 181, 322 -> 326 us, whatever the split into
-// claims; 2 piece groups, 64 / 512 / 1024 positions 29.9 -> 26.3, 34 -> 31,
-// 40 -> 38.5 us.  So 512 blocks of 64 piece groups still gain and 1024 lose.
+// Tail: the claims in one round of 1024 lanes, at most kTailRefs positions and
+// kTailPartials partials (one CU reads them), and not too many tokens (one CU
+// hashes them).  Measured, one check waited for (separate launches ->
+// k_check_small): 64 piece groups, 8 / 128 / 256 / 512 / 1024 blocks of 16
+// tokens 32.6 -> 27.3, 67.8 -> 63.1, 106 -> 102, 183 -> 181, 322 -> 326 us,
+// whatever the split into claims; 2 piece groups, 64 / 512 / 1024 positions
+// 29.9 -> 26.3, 34 -> 31, 40 -> 38.5 us.  So 512 blocks of 64 piece groups
+// still gain and 1024 lose.  Tokens, 1 piece group, us: 256 positions of 16 /
+// 256 / 1024 tokens 27.6 / 24.6, 33.9 / 31.6, 54.9 / 55.4; 512 of 16 / 64 / 128
+// / 256 28.8 / 27.9, 30.0 / 30.1, 31.4 / 33.7, 34.8 / 40.9; 768 of 16 / 32 / 64
+// 29.2 / 27.7, 28.1 / 28.6, 30.8 / 32.3; 1024 of 16 / 32 / 64 28.9 / 28.3, 29.9 /
+// 31.7, 30.8 / 35.3: the line is a product of positions and tokens.  Up to 4
+// waves of wide groups the time is that of one lane's tokens, which their loop
+// takes faster with the 168 registers of k_check than with the 128 of 1024
+// threads: 1 claim of 256 / 512 / 1024 blocks of 16 tokens 30.2 / 27.5, 36.2 /
+// 33.1, 47.7 / 44.3, of 256 / 512 of 64 33.0 / 33.1, 42.2 / 44.2, of 64 blocks of
+// 128 / 256 / 1024 27.6 / 26.5, 29.4 / 30.2, 41.9 / 51.9; 4 claims of 256 blocks
+// of 32 / 64 / 1024 34.1 / 31.7, 37.2 / 35.9, 157 / 185.
 constexpr uint64_t kTailRefs = 1024, kTailPartials = 32768;
+constexpr uint64_t kTailWork = 20ull << 20;  // positions x tokens
+constexpr uint64_t kTailLanes = 256;        // C x W of four waves
+constexpr uint64_t kTailLaneTokens = 256, kTailBlockSize = 128;
 
 bool select_is_small(const claim_pool* P, const claim_batch* b) {
   return P->nb <= kSelectBlocks && (uint64_t)b->num_claims * group_width(b) <= kSelectLanes &&
@@ -2836,10 +2850,20 @@ bool front_is_small(const claim_pool* P, const claim_batch* b) {
          (b->num_refs <= kFrontRefs + P->nb / 8 || select_is_small(P, b));
 }
 
-bool check_is_small(const claim_pool* P, const claim_batch* b) {
+bool tail_is_small(const claim_pool* P, const claim_batch* b) {
   const uint64_t ub = std::min<uint64_t>(b->num_refs, P->nb);
   return b->num_claims > 0 && b->num_refs <= kTailRefs &&
          (uint64_t)b->num_claims * group_width(b) <= 1024 && ub * P->pgs <= kTailPartials;
+}
+
+bool check_is_small(const claim_pool* P, const claim_batch* b) {
+  if (!tail_is_small(P, b)) return false;
+  const uint64_t W = group_width(b), lanes = b->num_claims * W;
+  if ((W < 16 || lanes >= kTailLanes) &&
+      b->num_tokens <= kTailWork / std::max<uint64_t>(1, b->num_refs))
+    return true;
+  return W >= 16 && lanes <= kTailLanes && P->bs <= kTailBlockSize &&
+         b->num_tokens <= kTailLaneTokens * lanes;
 }
 
 // Mark + compact the blocks referenced by the batch into P->uniq.
@@ -3582,12 +3606,12 @@ int claim_offload(claim_pool* P, const claim_batch* b, void* staging, uint64_t s
     TRY(launch_digest(P, gr, b->num_refs, P->partial, (uint8_t*)staging + slot0 * P->block_bytes));
   else if (fpo)  // not with the verdict
     TRY(launch_digest(P, gr, b->num_refs, P->partial, nullptr));
-  if (!fpo && check_is_small(P, b)) {
+  if (!fpo && tail_is_small(P, b)) {
     TRY(launch_admit_small(P, b, gr, staging != nullptr, (uint32_t)slot0));
   } else {
     TRY(launch_finalize(P, gr, 0, staging != nullptr, (uint32_t)slot0));
   }
-  if (C && (fpo || !check_is_small(P, b))) {
+  if (C && (fpo || !tail_is_small(P, b))) {
     // A large batch's first claims are accepted in a launch of their own:
     // identities that many claims share (common prefixes) are then in the
     // table before the rest start, instead of every resident wave racing

@@ -1,7 +1,8 @@
 """Small batches take one-workgroup kernels: the selection (up to 1024 lanes,
 and 65536 blocks to list, one more for 8 of the pool, for more than 4 claims),
 the restore (up to 1024 claims) and the check's tail (up to 1024 lanes and
-positions, 32768 partials); larger ones the kernels split over workgroups.
+positions, 32768 partials, and as many tokens as one CU hashes); larger ones
+the kernels split over workgroups.
 At and around those edges both must give the oracle's digests, outcomes and
 events: each group width, a claim of several windows, faults, missing
 entries, malformed and empty rows, an event log that just holds the call's
@@ -58,7 +59,10 @@ CASES += [("bitmap-full", 16, 6140), ("bitmap-full", 16, 6160), ("bitmap-full", 
 
 @pytest.mark.parametrize("pool,claims,blocks", CASES, ids=[f"{p}-{c}x{n}" for p, c, n in CASES])
 def test_small_batch(torch, ck, pool, claims, blocks):
-    g = POOLS[pool]
+    check_batch(torch, ck, POOLS[pool], pool, claims, blocks)
+
+
+def check_batch(torch, ck, g, pool, claims, blocks):
     rng = np.random.default_rng(claims * 1000 + blocks)
     w = Workload(name=f"small-{pool}", geometry=g, seed=77, num_claims=0, length=TINY.length,
                  sharing=TINY.sharing, corrupt_rate=0.0, gen_seed=1, content_seed=9)
@@ -103,6 +107,18 @@ def test_small_batch(torch, ck, pool, claims, blocks):
     assert np.array_equal(st["d_res"][recorded], d1[recorded])
     del kv
     free_gpu(torch)
+
+
+# the check's tail by its tokens: positions x tokens 20 Mi and past for narrow
+# groups and for 256 lanes and more; 256 tokens per lane, and blocks of 128
+# tokens and more, where wide groups fill up to 256 lanes
+TOKENS = [(32, 512, 1), (64, 512, 1), (128, 512, 1), (32, 24, 30), (64, 24, 30), (64, 1, 250),
+          (64, 1, 270), (129, 1, 30), (128, 4, 128), (128, 4, 130), (1024, 40, 2), (1024, 4, 16)]
+
+
+@pytest.mark.parametrize("bs,claims,blocks", TOKENS, ids=[f"{b}-{c}x{n}" for b, c, n in TOKENS])
+def test_small_tail_tokens(torch, ck, bs, claims, blocks):
+    check_batch(torch, ck, Geometry(2, 1, bs, 1, 16, 1, 700), f"{bs}-tokens", claims, blocks)
 
 
 # the front's edges: claims 1024 and past, lanes (claims x width) 8192 and past,
