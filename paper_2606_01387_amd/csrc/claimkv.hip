@@ -2866,6 +2866,26 @@ bool check_is_small(const claim_pool* P, const claim_batch* b) {
          b->num_tokens <= kTailLaneTokens * lanes;
 }
 
+// An offload's tail: one CU's waves also insert and register every claim's
+// identities, one atomic after another, so with many positions, claims or
+// tokens the separate launches are faster, unless the claims fill no more than
+// one of their workgroups.  Measured, one offload (separate launches /
+// k_admit_small, us): 256 positions in blocks of 16 tokens 59-62 / 57-61, of 256
+// 68-71 / 64-72, of 1024 91-108 / 87-106; 512 of 16 in 8 / 16 / 64 / 256 / 512
+// claims 66 / 63, 65 / 61, 65 / 62, 64 / 63, 65 / 66, of 64 in 16 / 64 / 512 64 /
+// 64, 66 / 64, 66 / 71, of 256 in 16 / 64 70 / 75, 73 / 76; 768 of 16 62 / 65-67;
+// 1024 of 16 63 / 67-73; 4 claims of 96 / 128 / 256 blocks of 16 69 / 65, 74 / 70,
+// 96 / 93, one of 256 / 512 / 1024 88 / 83, 134 / 127, 208 / 197.
+constexpr uint64_t kAdmitRefs = 256;
+constexpr uint64_t kAdmitMoreRefs = 512, kAdmitClaims = 256, kAdmitTokens = 32768;
+
+bool admit_is_small(const claim_pool* P, const claim_batch* b) {
+  return tail_is_small(P, b) &&
+         (b->num_refs <= kAdmitRefs || b->num_claims <= kOneGroupClaims ||
+          (b->num_refs <= kAdmitMoreRefs && b->num_claims <= kAdmitClaims &&
+           b->num_tokens <= kAdmitTokens));
+}
+
 // Mark + compact the blocks referenced by the batch into P->uniq.
 int select_blocks(claim_pool* P, const claim_batch* b, int mode, Counters* host = nullptr) {
   if (!host && select_is_small(P, b)) {
@@ -3606,12 +3626,13 @@ int claim_offload(claim_pool* P, const claim_batch* b, void* staging, uint64_t s
     TRY(launch_digest(P, gr, b->num_refs, P->partial, (uint8_t*)staging + slot0 * P->block_bytes));
   else if (fpo)  // not with the verdict
     TRY(launch_digest(P, gr, b->num_refs, P->partial, nullptr));
-  if (!fpo && tail_is_small(P, b)) {
+  const bool small = !fpo && admit_is_small(P, b);
+  if (small) {
     TRY(launch_admit_small(P, b, gr, staging != nullptr, (uint32_t)slot0));
   } else {
     TRY(launch_finalize(P, gr, 0, staging != nullptr, (uint32_t)slot0));
   }
-  if (C && (fpo || !tail_is_small(P, b))) {
+  if (C && !small) {
     // A large batch's first claims are accepted in a launch of their own:
     // identities that many claims share (common prefixes) are then in the
     // table before the rest start, instead of every resident wave racing

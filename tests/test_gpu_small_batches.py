@@ -123,9 +123,11 @@ def test_small_tail_tokens(torch, ck, bs, claims, blocks):
 
 # the front's edges: claims 1024 and past, lanes (claims x width) 8192 and past,
 # 8229 positions and past (8192 and one for 8 of the 300 blocks) where claims
-# have more than 1024 lanes; the tail's: as above
+# have more than 1024 lanes; the tail's: 256 positions and past for more than
+# 256 claims, 512 and past for more than 4, 1024 and past for up to 4
 FRONT = [(1, 3), (16, 64), (17, 64), (32, 20), (33, 20), (128, 64), (129, 64), (512, 2), (513, 2),
-         (1024, 4), (1024, 9), (1025, 1), (128, 66), (24, 340), (24, 512), (16, 1000)]
+         (1024, 4), (1024, 9), (1025, 1), (128, 66), (24, 340), (24, 512), (16, 1000),
+         (256, 1), (257, 1), (128, 4), (64, 9), (5, 104), (4, 200), (4, 256), (4, 258)]
 
 
 def family_batch(g, claims, blocks, rng, base, first=None):
