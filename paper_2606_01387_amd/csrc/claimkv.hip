@@ -2921,33 +2921,34 @@ int select_blocks(claim_pool* P, const claim_batch* b, int mode, Counters* host 
   return hip_status(hipGetLastError());
 }
 
-// Whether a staged offload of up to refs blocks writes staging past the
-// caches: then the pool's reads keep more of the memory's time, but a restore
-// that follows finds nothing of a small staging buffer in the 256 MB last-level
-// cache.  Staged offload and restore, staging kept in the caches / not, us:
-// 0.26 GB 284 / 297, 0.32 GB 321 / 341, 0.42 GB 405 / 411, 0.52 GB 494 / 491,
-// 1.05 GB 887 / 879; the offload of 2.35 GB 1107 / 997, of 13.5 GB (MLA) 5477 /
-// 5230.
+// Whether a staged offload of U blocks writes staging past the caches: then
+// the pool's reads keep more of the memory's time, but a restore that follows
+// finds nothing of a small staging buffer in the 256 MB last-level cache.
+// Staged offload and restore, staging kept in the caches / not, us: 0.26 GB 284
+// / 297, 0.32 GB 321 / 341, 0.42 GB 405 / 411, 0.52 GB 494 / 491, 1.05 GB 887 /
+// 879; the offload of 2.35 GB 1107 / 997, of 13.5 GB (MLA) 5477 / 5230.
 constexpr uint64_t kStageStreamBytes = 448ull << 20;
 
-bool stream_stage(const claim_pool* P, uint64_t refs) {
-  return (long double)std::min<uint64_t>(refs, P->nb) * P->block_bytes >
-         (long double)kStageStreamBytes;
+StageMode stage_mode(const claim_pool* P, uint64_t U) {
+  return (long double)U * P->block_bytes > (long double)kStageStreamBytes ? kStageStream
+                                                                         : kStageCached;
 }
 
-// Whether a restore of up to refs staged blocks copies them in pieces rather
-// than word by word.  Word by word / in pieces, us: 0.13 GB 61 / 69, 0.18-0.2 GB
-// 88-100 / 94-106 (the staged bytes are in the last-level cache, and more,
-// shorter workgroups hide its latency better), 0.26 GB 138 / 112, 0.52 GB 238 /
-// 225, 2 GB in 8 KiB chunks 804 / 784, in 16 KiB chunks 792 / 772, in 4 KiB
-// chunks (where a piece is 8 scattered runs) 798 / 799.  Blocks of fewer than 4
-// pieces would leave more than a quarter of the threads idle.
-constexpr uint64_t kPiecesBytes = 224ull << 20;
+// Whether a restore of up to n staged blocks copies them in pieces rather than
+// word by word.  A restore after its offload, word by word / in pieces, us:
+// 32 KiB chunks 120 / 140 / 160 / 200 / 240 / 280 MiB 58 / 59, 66 / 65, 75 / 71,
+// 99 / 91, 121 / 104, 141 / 126 (scattered over a pool of 4 GB 66 / 59, 74 / 65,
+// 81 / 73, 95 / 92, 114 / 107, 142 / 125), 8 KiB chunks 59 / 60, 71 / 69, 76 / 74,
+// 101 / 92, 124 / 108, 147 / 131, 36 KiB chunks 62 / 60, 67 / 69, 74 / 72, 97 / 95,
+// 121 / 107, 140 / 131; 2 GB in 8 KiB chunks 804 / 784, in 16 KiB chunks 792 / 772,
+// in 4 KiB chunks (where a piece is 8 scattered runs) 798 / 799.  Blocks of fewer
+// than 4 pieces would leave more than a quarter of the threads idle.
+constexpr uint64_t kPiecesBytes = 112ull << 20;
 constexpr uint64_t kPiecesChunk = 8 << 10;
 
-bool use_pieces(const claim_pool* P, uint64_t refs) {
+bool use_pieces(const claim_pool* P, uint64_t n) {
   return P->chunk_bytes >= kPiecesChunk && P->block_bytes >= 4 * 16 * kUnstageVecs &&
-         (long double)std::min<uint64_t>(refs, P->nb) * P->block_bytes > (long double)kPiecesBytes;
+         (long double)n * P->block_bytes > (long double)kPiecesBytes;
 }
 
 // The digest grid of one launch: pga piece groups read at a time, groups
@@ -2957,8 +2958,8 @@ struct DigestGrid {
 };
 
 template <int LPW>
-int launch_digest_lpw(claim_pool* P, DigestGrid gr, uint64_t refs, uint64_t* partial, void* staging,
-                      int* wgs_per_cu) {
+int launch_digest_lpw(claim_pool* P, DigestGrid gr, StageMode mode, uint64_t* partial,
+                      void* staging, int* wgs_per_cu) {
   if (wgs_per_cu)  // occupancy query only
     return hip_status(hipOccupancyMaxActiveBlocksPerMultiprocessor(
         wgs_per_cu, (const void*)k_digest<LPW, kNoStage>, kThreads, 0));
@@ -2968,8 +2969,8 @@ int launch_digest_lpw(claim_pool* P, DigestGrid gr, uint64_t refs, uint64_t* par
   hipLaunchKernelGGL((k_digest<LPW, S>), grid, block, 0, P->stream, (const u32x2*)P->kv, P->nb,   \
                      cw, P->planes, P->segs, gr.pga, gr.groups, P->uniq, P->ctr, P->seed,         \
                      P->kmap, partial, (u32x2*)staging)
-  if (!staging) GO(kNoStage);
-  else if (stream_stage(P, refs)) GO(kStageStream);
+  if (mode == kNoStage) GO(kNoStage);
+  else if (mode == kStageStream) GO(kStageStream);
   else GO(kStageCached);
 #undef GO
   return hip_status(hipGetLastError());
@@ -2989,25 +2990,25 @@ int launch_digest_run(claim_pool* P, DigestGrid gr, uint64_t* partial, void* sta
 }
 
 template <int LPW, bool ROWS>
-int launch_digest_rows(claim_pool* P, DigestGrid gr, uint64_t refs, uint64_t* partial,
+int launch_digest_rows(claim_pool* P, DigestGrid gr, StageMode mode, uint64_t* partial,
                        void* staging, int* wgs_per_cu) {
-  if (!staging)
+  if (mode == kNoStage)
     return launch_digest_run<LPW, ROWS, kNoStage>(P, gr, partial, staging, wgs_per_cu);
-  if (stream_stage(P, refs))
+  if (mode == kStageStream)
     return launch_digest_run<LPW, ROWS, kStageStream>(P, gr, partial, staging, wgs_per_cu);
   return launch_digest_run<LPW, ROWS, kStageCached>(P, gr, partial, staging, wgs_per_cu);
 }
 
-// Launch the digest of up to refs blocks on grid gr (or, with wgs_per_cu,
-// query its occupancy).
-int launch_digest(claim_pool* P, DigestGrid gr, uint64_t refs, uint64_t* partial, void* staging,
-                  int* wgs_per_cu = nullptr) {
+// Launch the digest on grid gr, staging its blocks by mode (or, with
+// wgs_per_cu, query its occupancy).
+int launch_digest(claim_pool* P, DigestGrid gr, uint64_t* partial, StageMode mode = kNoStage,
+                  void* staging = nullptr, int* wgs_per_cu = nullptr) {
   if (P->segs == 0) {  // pieces that run across chunk ends
     const bool rows = P->chunk_vecs % 32 == 0;
 #define RUN_CASE(l)                                                                    \
   if (P->lpw == l)                                                                     \
-    return rows ? launch_digest_rows<l, true>(P, gr, refs, partial, staging, wgs_per_cu) \
-                : launch_digest_rows<l, false>(P, gr, refs, partial, staging, wgs_per_cu);
+    return rows ? launch_digest_rows<l, true>(P, gr, mode, partial, staging, wgs_per_cu) \
+                : launch_digest_rows<l, false>(P, gr, mode, partial, staging, wgs_per_cu);
     RUN_CASE(1) RUN_CASE(2) RUN_CASE(4) RUN_CASE(8) RUN_CASE(20)
 #undef RUN_CASE
     return CLAIM_EINVAL;
@@ -3015,7 +3016,7 @@ int launch_digest(claim_pool* P, DigestGrid gr, uint64_t refs, uint64_t* partial
   switch (P->lpw) {
 #define DIGEST_CASE(l) \
   case l:              \
-    return launch_digest_lpw<l>(P, gr, refs, partial, staging, wgs_per_cu);
+    return launch_digest_lpw<l>(P, gr, mode, partial, staging, wgs_per_cu);
     DIGEST_CASE(4) DIGEST_CASE(8) DIGEST_CASE(16) DIGEST_CASE(24)
 #undef DIGEST_CASE
     default:
@@ -3173,7 +3174,8 @@ int choose_digest_shape(claim_pool* P) {
   P->lpw = best;
   P->pgs = (P->ps_total + 3) / 4;
   int per_cu = 0;
-  TRY(launch_digest(P, DigestGrid{1, 1}, 0, nullptr, nullptr, &per_cu));  // the kernel's occupancy
+  // the kernel's occupancy
+  TRY(launch_digest(P, DigestGrid{1, 1}, nullptr, kNoStage, nullptr, &per_cu));
   const int wg_bytes = 4 * best * 64 * 8;  // loads in flight per workgroup
   const int want = kInflightPerCu / wg_bytes > 1 ? kInflightPerCu / wg_bytes : 1;
   if (per_cu > want) per_cu = want;
@@ -3590,7 +3592,7 @@ int claim_offload(claim_pool* P, const claim_batch* b, void* staging, uint64_t s
   HIP_TRY(hipEventRecord(P->verdict, P->stream));
   const DigestGrid gr = digest_grid(P, b->num_refs);
   const bool ahead = !staging && P->fp_used + b->num_refs <= P->max_fp;
-  if (ahead) TRY(launch_digest(P, gr, b->num_refs, P->partial, nullptr));
+  if (ahead) TRY(launch_digest(P, gr, P->partial));
   HIP_TRY(hipEventSynchronize(P->verdict));  // the kernels published the counters
   // (what is still queued has no blocks: it reads nothing of the caller's)
   if (P->host_ctr->dup_flag & kFlagDupId) return CLAIM_EDUP;
@@ -3623,9 +3625,10 @@ int claim_offload(claim_pool* P, const claim_batch* b, void* staging, uint64_t s
   P->gen += 1;
   if (staging && !append) TRY(fill<uint32_t>(P, P->slot_of, P->nb, kNone));
   if (staging)
-    TRY(launch_digest(P, gr, b->num_refs, P->partial, (uint8_t*)staging + slot0 * P->block_bytes));
+    TRY(launch_digest(P, gr, P->partial, stage_mode(P, U),
+                      (uint8_t*)staging + slot0 * P->block_bytes));
   else if (fpo)  // not with the verdict
-    TRY(launch_digest(P, gr, b->num_refs, P->partial, nullptr));
+    TRY(launch_digest(P, gr, P->partial));
   const bool small = !fpo && admit_is_small(P, b);
   if (small) {
     TRY(launch_admit_small(P, b, gr, staging != nullptr, (uint32_t)slot0));
@@ -3704,10 +3707,11 @@ int claim_restore(claim_pool* P, const claim_batch* b, const void* staging,
   if (staging) {
     TRY(select_blocks(P, b, kMarkStaged));
     const uint64_t block_vecs = P->planes * P->chunk_vecs;
-    if (use_pieces(P, b->num_refs)) {
+    const uint64_t n = std::min(std::min<uint64_t>(P->nb, b->num_refs), P->stage_used);
+    if (use_pieces(P, n)) {
       const uint64_t pieces = (block_vecs + kUnstageVecs - 1) / kUnstageVecs;
-      const uint64_t most = std::min<uint64_t>(P->nb, b->num_refs) * pieces;
-      hipLaunchKernelGGL(k_unstage, dim3((uint32_t)std::min<uint64_t>(most, 2 * P->cus)), dim3(kThreads), 0, P->stream, (u32x4*)P->kv, P->nb,
+      const uint32_t grid = (uint32_t)std::min<uint64_t>(n * pieces, 2 * P->cus);
+      hipLaunchKernelGGL(k_unstage, dim3(grid), dim3(kThreads), 0, P->stream, (u32x4*)P->kv, P->nb,
                          (uint32_t)P->chunk_vecs, P->planes, P->uniq, P->ctr, P->slot_of,
                          (const u32x4*)staging);
     } else {
@@ -3800,7 +3804,7 @@ int check_body(claim_pool* P, const claim_batch* b, claim_outcome* out, ClaimScr
   TRY(select_blocks(P, b, kMarkOffloaded));  // recorded blocks of the well-formed rows
   TRY(record_stage(P, slot, 1));
   const DigestGrid gr = digest_grid(P, b->num_refs);
-  TRY(launch_digest(P, gr, b->num_refs, P->partial, nullptr));
+  TRY(launch_digest(P, gr, P->partial));
   TRY(record_stage(P, slot, 2));
   CheckState st;
   st.bres = P->bres;

@@ -19,6 +19,8 @@ CASES = [
     Geometry(1, 1, 2, 1, 8, 1, 300),  # blocks of one word
     Geometry(1025, 1, 2, 1, 8, 1, 40),  # 16-byte chunks
     Geometry(7, 1, 64, 1, 576, 1, 60),  # few bytes
+    Geometry(8, 2, 16, 1, 256, 2, 890),  # just under and past 112 MiB
+    Geometry(8, 2, 16, 1, 256, 2, 905),
     Geometry(8, 2, 1, 1, 8176, 1, 1900),  # chunks just under 8 KiB
     Geometry(15, 1, 16, 1, 256, 2, 2000),  # blocks of just under 4 pieces
     Geometry(8, 2, 16, 1, 256, 2, 1900),  # 4 whole chunks a piece, 4 pieces a block
@@ -62,4 +64,38 @@ def test_unstage(torch, ck, g):
                 assert torch.equal(pool[l, back], want[l, back])
                 assert bool((pool[l, ~back] == 0x5A).all())
     del kv, pool, want, staging, rows
+    free_gpu(torch)
+
+
+@pytest.mark.parametrize("blocks", [60, 119, 230])
+def test_many_references(torch, ck, blocks):
+    """Few blocks under many references (2 to 4 GB of them): the blocks that
+    are staged decide how they are copied."""
+    g = Geometry(32, 2, 16, 8, 128, 2, 700)
+    rng = np.random.default_rng(blocks)
+    w = Workload(name="references", geometry=g, seed=5, num_claims=0, length=TINY.length,
+                 sharing=TINY.sharing, corrupt_rate=0.0, gen_seed=1, content_seed=7)
+    note(f"many references to {blocks} blocks")
+    kv = gpu_pool_tensor(torch, w)
+    pool = kv.view(g.planes, g.num_blocks, g.chunk_bytes)
+    want = pool.clone()
+    used = np.sort(rng.choice(g.num_blocks, blocks, replace=False))
+    batch = from_claims([(i + 1, rng.permutation(used)[:50], rng.integers(0, 32000, 50 * 16))
+                         for i in range(40)])
+    used = batch.unique_blocks(g.num_blocks)
+    staging = torch.zeros(used.size * g.block_bytes, dtype=torch.uint8, device="cuda")
+    with ck.Pool(g, w.seed, kv, max_claims=64, max_footprint=4096, event_capacity=4096) as p:
+        db = ck.DeviceBatch(batch)
+        p.offload(db, staging=staging)
+        pool.fill_(0x5A)
+        p.restore(db, staging=staging)
+        p.check(db)
+        out, _ = p.read()
+    assert (out["code"] == ck.MATERIALIZED).all()
+    back = torch.zeros(g.num_blocks, dtype=torch.bool, device="cuda")
+    back[torch.from_numpy(used.astype(np.int64)).cuda()] = True
+    for l in range(g.planes):
+        assert torch.equal(pool[l, back], want[l, back])
+        assert bool((pool[l, ~back] == 0x5A).all())
+    del kv, pool, want, staging
     free_gpu(torch)
