@@ -2921,17 +2921,32 @@ int select_blocks(claim_pool* P, const claim_batch* b, int mode, Counters* host 
   return hip_status(hipGetLastError());
 }
 
+// Whether p lies in memory of a GPU (an attribute query takes 0.3 us; only
+// copies of tens of microseconds ask).
+bool device_memory(const void* p) {
+  hipPointerAttribute_t a;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice;
+}
+
 // Whether a staged offload of U blocks writes staging past the caches: then
 // the pool's reads keep more of the memory's time, but a restore that follows
 // finds nothing of a small staging buffer in the 256 MB last-level cache.
 // Staged offload and restore, staging kept in the caches / not, us: 0.26 GB 284
 // / 297, 0.32 GB 321 / 341, 0.42 GB 405 / 411, 0.52 GB 494 / 491, 1.05 GB 887 /
-// 879; the offload of 2.35 GB 1107 / 997, of 13.5 GB (MLA) 5477 / 5230.
+// 879; the offload of 2.35 GB 1107 / 997, of 13.5 GB (MLA) 5477 / 5230.  Staging
+// in host memory is bound by the host link and measured no better for it:
+// 0.26 GB 4714 / 4782, 0.5 GB in 4 to 36 KiB chunks 8878-9386 / 8940-9471, 1 GB
+// 17973 / 18109.
 constexpr uint64_t kStageStreamBytes = 448ull << 20;
 
-StageMode stage_mode(const claim_pool* P, uint64_t U) {
-  return (long double)U * P->block_bytes > (long double)kStageStreamBytes ? kStageStream
-                                                                         : kStageCached;
+StageMode stage_mode(const claim_pool* P, uint64_t U, const void* staging) {
+  return (long double)U * P->block_bytes > (long double)kStageStreamBytes && device_memory(staging)
+             ? kStageStream
+             : kStageCached;
 }
 
 // Whether a restore of up to n staged blocks copies them in pieces rather than
@@ -2942,13 +2957,15 @@ StageMode stage_mode(const claim_pool* P, uint64_t U) {
 // 101 / 92, 124 / 108, 147 / 131, 36 KiB chunks 62 / 60, 67 / 69, 74 / 72, 97 / 95,
 // 121 / 107, 140 / 131; 2 GB in 8 KiB chunks 804 / 784, in 16 KiB chunks 792 / 772,
 // in 4 KiB chunks (where a piece is 8 scattered runs) 798 / 799.  Blocks of fewer
-// than 4 pieces would leave more than a quarter of the threads idle.
+// than 4 pieces would leave more than a quarter of the threads idle.  From host
+// memory, 0.26 GB 4606 / 4755, 0.5 GB in 8 to 36 KiB chunks 8817-9371 / 8897-9428
+// (with twice the grid the same), 1 GB 18012 / 18029.
 constexpr uint64_t kPiecesBytes = 112ull << 20;
 constexpr uint64_t kPiecesChunk = 8 << 10;
 
-bool use_pieces(const claim_pool* P, uint64_t n) {
+bool use_pieces(const claim_pool* P, uint64_t n, const void* staging) {
   return P->chunk_bytes >= kPiecesChunk && P->block_bytes >= 4 * 16 * kUnstageVecs &&
-         (long double)n * P->block_bytes > (long double)kPiecesBytes;
+         (long double)n * P->block_bytes > (long double)kPiecesBytes && device_memory(staging);
 }
 
 // The digest grid of one launch: pga piece groups read at a time, groups
@@ -3625,7 +3642,7 @@ int claim_offload(claim_pool* P, const claim_batch* b, void* staging, uint64_t s
   P->gen += 1;
   if (staging && !append) TRY(fill<uint32_t>(P, P->slot_of, P->nb, kNone));
   if (staging)
-    TRY(launch_digest(P, gr, P->partial, stage_mode(P, U),
+    TRY(launch_digest(P, gr, P->partial, stage_mode(P, U, staging),
                       (uint8_t*)staging + slot0 * P->block_bytes));
   else if (fpo)  // not with the verdict
     TRY(launch_digest(P, gr, P->partial));
@@ -3708,7 +3725,7 @@ int claim_restore(claim_pool* P, const claim_batch* b, const void* staging,
     TRY(select_blocks(P, b, kMarkStaged));
     const uint64_t block_vecs = P->planes * P->chunk_vecs;
     const uint64_t n = std::min(std::min<uint64_t>(P->nb, b->num_refs), P->stage_used);
-    if (use_pieces(P, n)) {
+    if (use_pieces(P, n, staging)) {
       const uint64_t pieces = (block_vecs + kUnstageVecs - 1) / kUnstageVecs;
       const uint32_t grid = (uint32_t)std::min<uint64_t>(n * pieces, 2 * P->cus);
       hipLaunchKernelGGL(k_unstage, dim3(grid), dim3(kThreads), 0, P->stream, (u32x4*)P->kv, P->nb,

@@ -38,22 +38,39 @@ CASES = [
 
 @pytest.mark.parametrize("g", CASES, ids=[f"{g.chunk_bytes}Bx{g.planes}x{g.num_blocks}" for g in CASES])
 def test_unstage(torch, ck, g):
+    round_trips(torch, ck, g, "device")
+
+
+# page-locked host memory past the lines that device staging has (112 MiB back,
+# 448 MiB out): whole pieces and pieces across chunk ends
+HOST = [Geometry(7, 1, 64, 1, 576, 1, 600), Geometry(32, 2, 16, 8, 128, 2, 240),
+        Geometry(61, 1, 8, 1, 576, 1, 1750)]
+
+
+@pytest.mark.parametrize("g", HOST, ids=[f"{g.chunk_bytes}Bx{g.planes}x{g.num_blocks}" for g in HOST])
+def test_unstage_host(torch, ck, g):
+    round_trips(torch, ck, g, "host")
+
+
+def round_trips(torch, ck, g, where):
     rng = np.random.default_rng(g.chunk_bytes + g.planes)
     w = Workload(name="unstage", geometry=g, seed=5, num_claims=0, length=TINY.length,
                  sharing=TINY.sharing, corrupt_rate=0.0, gen_seed=1, content_seed=7)
-    note(f"unstage {g.chunk_bytes} B x {g.planes} planes, {g.num_blocks} blocks")
+    note(f"unstage from {where} memory {g.chunk_bytes} B x {g.planes} planes, {g.num_blocks} blocks")
     kv = gpu_pool_tensor(torch, w)
     pool = kv.view(g.planes, g.num_blocks, g.chunk_bytes)
     want = pool.clone()
     order = rng.permutation(g.num_blocks)[: g.num_blocks - 3]
     claims = [(i + 1, [int(b)], rng.integers(0, 32000, g.block_size)) for i, b in enumerate(order)]
     batch, part = from_claims(claims), from_claims([claims[4], claims[0]])
-    staging = torch.zeros(order.size * g.block_bytes, dtype=torch.uint8, device="cuda")
+    staging = torch.zeros(order.size * g.block_bytes, dtype=torch.uint8,
+                          **(dict(device="cuda") if where == "device" else dict(pin_memory=True)))
     with ck.Pool(g, w.seed, kv, max_claims=4096, max_footprint=4096, event_capacity=32768) as p:
         p.offload(ck.DeviceBatch(batch), staging=staging)
         used = torch.from_numpy(np.sort(order)).cuda()
         rows = staging.view(order.size, g.planes, g.chunk_bytes)
-        assert all(torch.equal(rows[:, l], want[l, used]) for l in range(g.planes))
+        torch.cuda.synchronize()
+        assert all(torch.equal(rows[:, l].cuda(), want[l, used]) for l in range(g.planes))
         for b, blocks in ((part, order[[4, 0]]), (from_claims([]), order[:0]), (batch, order)):
             pool.fill_(0x5A)
             p.restore(ck.DeviceBatch(b), staging=staging)
