@@ -3116,7 +3116,7 @@ int append_events(claim_pool* P, const claim_batch* b, ClaimScratch sc, Counters
 
 // Choose words per lane (LPW), segments per chunk and the digest grid.
 // LPW is 24, 16 or 8, the largest of them that divides the chunk's words per
-// lane (4 for chunks of 4, 20 or 28 rows), so every segment is full and each
+// lane (4 for chunks of 4, 12, 20 or 28 rows), so every segment is full and each
 // wave streams up to 12 KiB per block.  Measured on MI355X in one process
 // over one allocation, two repetitions each: 16 words (8 KiB pieces, 32 KiB
 // in flight per CU) instead of 32 (16 KiB pieces, 64 KiB) read the 8B pool
@@ -3132,7 +3132,10 @@ int append_events(claim_pool* P, const claim_batch* b, ClaimScratch sc, Counters
 // inside a row (22.5 and 31.5 rows) 20 words 7017 and 6118, 7022 and 6122, 8
 // words 6859 and 6240, 6927 and 6333: those take 20 words in pools past
 // kWideRunBytes.  Chunks of 4 rows read the same either way (4 GB 6893 and
-// 6935, 0.5 GB 6357 and 6132 with 20 words).  The grid is persistent and
+// 6935, 0.5 GB 6357 and 6132 with 20 words), and of 12 rows nearly (GB/s, 4
+// words, one piece of 12, runs of 8 and of 20: 64 planes, 4.3 GB 7040, 6192, 7218,
+// 7122, 0.54 GB 6720, 5682, 6730, 6415, 0.06 GB 4119, 3299, 3669, 3111; 61 planes,
+// 4.1 GB 6630, 5834, 6719, 6630; 5 planes, 4.3 GB 7229, 3508, 7110, 6893).  The grid is persistent and
 // fully resident (no tail of late waves): slots = workgroups per CU x CUs,
 // shared by the piece groups read at a time (digest_grid).
 // Workgroups per CU: enough for about

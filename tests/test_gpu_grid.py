@@ -30,6 +30,8 @@ CASES = [
     # 17.1 GB of 36 KiB chunks in three 12 KiB pieces: half of the 46 piece
     # groups would end inside a chunk, so one phase
     ("mla-shaped-17.1GB", Geometry(61, 1, 64, 1, 576, 1, 7600), None, (24, 3, 46, 256, 46, 5)),
+    # 6 KiB chunks (12 rows): three pieces of 4 words, 4 workgroups per CU
+    ("12-rows-4.3GB", Geometry(32, 2, 16, 3, 64, 2, 10922), None, (4, 3, 48, 1024, 48, 21)),
     # 15.9 GB in an odd number of piece groups (27): one phase
     ("odd-piece-groups-15.9GB", Geometry(27, 2, 16, 4, 128, 2, 18000), None, (16, 2, 27, 256, 27, 9)),
     (MANY_PLANES.name, MANY_PLANES.geometry, None, (16, 4, 320, 256, 80, 3)),
