@@ -1,12 +1,12 @@
-"""The digest kernel over seeded random pool geometries, against the
+"""The digest kernels over seeded random pool geometries, against the
 oracle: block sizes, head counts, head widths and element sizes that give
-chunks from 16 bytes to 72 KiB (every words-per-lane width the kernel
-instantiates, whole and ragged chunks, one or several segments per chunk),
-planes from 1 to 12, and head shards at random offsets; and pools of 100 to
-860 planes over 8 to 16 blocks, whose digest mostly reads its piece groups
-in phases (one phase would leave much of the grid idle).  Every block's
-offload digest, and its restore digest after seeded flips, must equal the
-oracle's."""
+chunks from 16 bytes to 72 KiB (pieces of 4, 8, 16 and 24 words per lane that
+divide the chunk, one or several to a chunk; pieces of 1, 2, 4 and 8 words that
+run across chunk ends, where none divides it), planes from 1 to 12, and head
+shards at random offsets; and pools of 115 to 1365 planes over 8 to 16 blocks,
+with both kinds of pieces, most of which read their piece groups in phases (one
+phase would leave much of the grid idle).  Every block's offload digest, and
+its restore digest after seeded flips, must equal the oracle's."""
 
 import os
 
@@ -40,26 +40,34 @@ def random_geometry(rng) -> Geometry:
         return Geometry(layers, ppl, bs, heads, dim, eb, nb)
 
 
-# Chunks of 12 to 72 words per lane (6 to 36 KiB) and the segments they
-# split into: pieces of 12, 16, 24 or 32 words per lane, one digest
-# workgroup per CU.
-_PLANE_CHUNKS = [(6144, 1), (8192, 1), (12288, 1), (16384, 1), (24576, 2), (32768, 2), (36864, 3)]
+# Chunks of 6 to 36 KiB and the pieces that divide them (4, 16, 16, 24 or 24
+# words per lane), and 9-row chunks in pieces of 8 rows across chunk ends, with
+# the digest workgroups that 256 CUs hold at once.
+_PLANE_CHUNKS = [(6144, 3, 1024), (8192, 1, 256), (12288, 1, 256), (16384, 2, 256), (24576, 2, 256),
+                 (32768, 4, 256), (36864, 3, 256), (4608, 9 / 8, 512), (4608, 9 / 8, 512)]
 
 
-def many_plane_geometry(rng) -> Geometry:
-    """Planes enough for 87-108 or 130-216 piece groups of 4 pieces (the
-    last group often short): one phase would fill at most 85 % of a grid of
-    one workgroup per CU on 256 CUs."""
+def many_plane_geometry(rng) -> tuple[Geometry, bool]:
+    """Planes enough for 34-42 % or 51-84 % as many piece groups of 4 pieces
+    (the last group often short) as workgroups fit: one phase would fill at
+    most 85 % of the grid.  Most have a multiple of 12 of them, which splits into
+    phases that fill it; whether it has is returned too."""
     while True:
-        chunk, segs = _PLANE_CHUNKS[int(rng.integers(len(_PLANE_CHUNKS)))]
-        pgs = int(rng.integers(87, 109)) if rng.random() < 0.3 else int(rng.integers(130, 217))
-        planes = max(1, (4 * pgs - int(rng.integers(0, 4))) // segs)
+        chunk, segs, slots = _PLANE_CHUNKS[int(rng.integers(len(_PLANE_CHUNKS)))]
+        lo, hi = (0.34, 0.42) if rng.random() < 0.3 else (0.51, 0.84)
+        pgs = int(rng.integers(int(lo * slots), int(hi * slots)))
+        phased = rng.random() < 0.7
+        if phased:
+            pgs += -pgs % 12
+        planes = int((4 * pgs - int(rng.integers(0, 4))) / segs)
+        if pgs > hi * slots or -(-int(np.ceil(planes * segs)) // 4) != pgs:
+            continue
         ppl = 2 if planes % 2 == 0 and rng.random() < 0.5 else 1
         bs = int(rng.choice([1, 2, 4, 8, 16]))
         nb = int(rng.integers(8, 17))  # enough blocks for several workgroups per phase
         if planes * chunk * nb > 160 << 20:
             continue
-        return Geometry(planes // ppl, ppl, bs, 1, chunk // bs, 1, nb)
+        return Geometry(planes // ppl, ppl, bs, 1, chunk // bs, 1, nb), phased
 
 
 # CLAIMKV_SHAPE_SEEDS widens a one-off run; the suite runs the first 60
@@ -69,10 +77,41 @@ def test_digest_shapes(torch, ck, seed):
     run_shape(torch, ck, random_geometry(rng), rng, seed)
 
 
-@pytest.mark.parametrize("seed", range(int(os.environ.get("CLAIMKV_PLANE_SEEDS", "16"))))
+def digest_grid(torch, ck, g):
+    kv = torch.empty(g.pool_bytes, dtype=torch.uint8, device="cuda")
+    with ck.Pool(g, 1, kv, max_claims=64, max_footprint=64, event_capacity=64) as pool:
+        return pool.digest_grid()
+
+
+def test_shapes_cover_the_widths(torch, ck):
+    """The first 60 seeds reach every width of pieces that divide a chunk, and
+    those across chunk ends but the widest (20 words: many rows)."""
+    grids = [digest_grid(torch, ck, random_geometry(np.random.default_rng(70_000 + s)))
+             for s in range(60)]
+    assert {d["words_per_lane"] for d in grids if d["segments"]} == {4, 8, 16, 24}
+    assert {d["words_per_lane"] for d in grids if not d["segments"]} >= {1, 2, 4, 8}
+    assert {d["segments"] > 1 for d in grids if d["segments"]} == {True, False}
+
+
+@pytest.mark.parametrize("seed", range(int(os.environ.get("CLAIMKV_PLANE_SEEDS", "24"))))
 def test_digest_shapes_many_planes(torch, ck, seed):
     rng = np.random.default_rng(80_000 + seed)
-    run_shape(torch, ck, many_plane_geometry(rng), rng, seed)
+    g, _ = many_plane_geometry(rng)
+    run_shape(torch, ck, g, rng, seed)
+
+
+def test_many_planes_are_read_in_phases(torch, ck):
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("grid expectations are for 256 compute units")
+    phased = {True: 0, False: 0}  # by whether pieces run across chunk ends
+    for seed in range(24):
+        g, several = many_plane_geometry(np.random.default_rng(80_000 + seed))
+        d = digest_grid(torch, ck, g)
+        phases = d["piece_groups"] // d["pga"]
+        assert d["pga"] * d["groups"] <= d["slots"]
+        assert phases > 1 or not several, (seed, g, d)
+        phased[d["segments"] == 0] += phases > 1
+    assert phased[False] >= 8 and phased[True] >= 3
 
 
 def run_shape(torch, ck, g, rng, seed):
