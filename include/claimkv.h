@@ -421,7 +421,8 @@ int claim_check_static(claim_pool* pool, const claim_batch* batch, claim_outcome
  * CLAIM_LOOKUP_UNKNOWN rather than a shorter hit (Table 2: duplicate owners
  * fail closed), as it is for a malformed row (reserved id, token offsets
  * that run backwards or past num_tokens).  The registry and event log are
- * not changed.  out is device memory with room for out_cap records; it is
+ * not changed.  out is device memory, or host memory from hipHostMalloc, with
+ * room for out_cap records; it is
  * written in stream order on the pool's stream and is complete once the
  * stream reaches this call (the call does not wait).  ENOSPC if out_cap <
  * num_claims; EINVAL for a NULL out with requests, or a bad batch. */

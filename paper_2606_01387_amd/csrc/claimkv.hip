@@ -16,12 +16,12 @@
 //    block's 512-byte rows across chunk ends; and since k_i depends
 //    only on the word's canonical position, a wave pinned to one piece keeps
 //    that piece's keys in VGPRs and streams the same piece of many blocks,
-//    with all LPW loads in flight before any use.  The 4 waves of a workgroup take 4 consecutive pieces
-//    of the same blocks and park their per-block sums in an LDS ring, which
-//    the workgroup adds and writes as one contiguous run of partials; the
-//    grid is exactly one resident round, and on larger pools it reads the
-//    piece groups in phases (two from 14 GiB, a few piece groups at a time
-//    past 32 GiB).  Each 64-bit word costs one
+//    with all LPW loads in flight before any use.  The 4 waves of a workgroup
+//    take 4 consecutive pieces of the same blocks and park their per-block
+//    sums in an LDS ring, which the workgroup adds and writes as one
+//    contiguous run of partials; the grid is exactly one resident round, and
+//    on larger pools it reads the piece groups in phases (two from 14 GiB, a
+//    few piece groups at a time past 32 GiB).  Each 64-bit word costs one
 //    32x32->64 multiply-add for lo(w) lo(k) and two 32-bit multiply-adds for
 //    the cross terms (only their low 32 bits reach the result mod 2^64).  A
 //    small kernel adds each block's partials.  No atomics: results are
@@ -853,7 +853,7 @@ __device__ __forceinline__ uint64_t dpp_wave_sum64(uint64_t v) {
 }
 
 // STAGE: also copy the words to staging (offload with staging), past the
-// caches where the batch's blocks are many (kStageStreamBytes).
+// caches where the blocks are many and staging is device memory (stage_mode).
 enum StageMode : int { kNoStage = 0, kStageCached = 1, kStageStream = 2 };
 
 template <int STAGE>
@@ -3135,9 +3135,10 @@ int append_events(claim_pool* P, const claim_batch* b, ClaimScratch sc, Counters
 // 6935, 0.5 GB 6357 and 6132 with 20 words), and of 12 rows nearly (GB/s, 4
 // words, one piece of 12, runs of 8 and of 20: 64 planes, 4.3 GB 7040, 6192, 7218,
 // 7122, 0.54 GB 6720, 5682, 6730, 6415, 0.06 GB 4119, 3299, 3669, 3111; 61 planes,
-// 4.1 GB 6630, 5834, 6719, 6630; 5 planes, 4.3 GB 7229, 3508, 7110, 6893).  The grid is persistent and
-// fully resident (no tail of late waves): slots = workgroups per CU x CUs,
-// shared by the piece groups read at a time (digest_grid).
+// 4.1 GB 6630, 5834, 6719, 6630; 5 planes, 4.3 GB 7229, 3508, 7110, 6893).
+// The grid is persistent and fully resident (no tail of late waves): slots =
+// workgroups per CU x CUs, shared by the piece groups read at a time
+// (digest_grid).
 // Workgroups per CU: enough for about
 // kInflightPerCu bytes of loads in flight per CU (each wave keeps
 // LPW x 512 bytes in flight), at most what can be resident.  Measured on
@@ -3588,9 +3589,9 @@ int claim_offload(claim_pool* P, const claim_batch* b, void* staging, uint64_t s
   const BatchDev bd = batch_dev(b);
   const RegDev rd = reg_dev(P);
   if (front_is_small(P, b)) {
-    hipLaunchKernelGGL(k_admit_select, dim3(1), dim3(1024), (P->nb + 31) / 32 * 4, P->stream, bd, rd,
-                       (uint32_t)__builtin_ctz((unsigned)group_width(b)), P->nb, P->uniq, P->ctr,
-                       P->host_ctr_dev);
+    hipLaunchKernelGGL(k_admit_select, dim3(1), dim3(1024), (P->nb + 31) / 32 * 4, P->stream, bd,
+                       rd, (uint32_t)__builtin_ctz((unsigned)group_width(b)), P->nb, P->uniq,
+                       P->ctr, P->host_ctr_dev);
     HIP_TRY(hipGetLastError());
   } else {
     hipLaunchKernelGGL(k_dup_clear, dim3(grid_for(P->dup_cap, 4096)), dim3(kThreads), 0, P->stream,
@@ -3679,7 +3680,8 @@ int claim_offload(claim_pool* P, const claim_batch* b, void* staging, uint64_t s
                      P->pend, P->cnt, P->uniq, P->owner_at, P->holder, P->ctr);
     } else {
       hipLaunchKernelGGL(k_register_claims, dim3(grid_for(C, 0x7FFFFFFFu)), dim3(kThreads), 0,
-                         P->stream, bd, rd, P->bs, P->fp_used, P->gen, fpo, P->pend, P->cnt, P->ctr);
+                         P->stream, bd, rd, P->bs, P->fp_used, P->gen, fpo, P->pend, P->cnt,
+                         P->ctr);
       HIP_TRY(hipGetLastError());
       LAUNCH_GROUPED(k_register_owners, P, b, bd, rd, id_dev(P), P->nb, P->bs, P->fp_used, fpo,
                      P->owner_at, P->ctr);

@@ -1,6 +1,7 @@
 """Staged blocks return to the pool in pieces of 2048 16-byte words of a block
-where the batch, its blocks and their chunks are large enough, word by word
-otherwise; large staged offloads write past the caches.  Sizes on both sides
+where they, their bytes and their chunks are large enough and staging is device
+memory, word by word otherwise; large staged offloads to device memory write
+past the caches.  Sizes on both sides
 of each line, pieces that end inside a chunk and cross chunk ends, and every
 kind of digest piece: staging must hold the blocks' bytes, every restored
 block its bytes again, in whatever order its claims stage and restore it, and
